@@ -8,201 +8,689 @@
 // Quantization") and asymmetric key/value formats (Related Work) but leaves
 // the rule open; this is the rule the library defines in kvq.h.
 //
-// Exactness: x - z is exact in fp64, the fp64 quotient is correctly rounded
-// (IEEE divide; this file is built with -ffp-contract=off and no fast-math)
-// and rint() rounds half to even, so codes equal the exact rational
-// round-half-even.  Off the decode hot path: a key group flushes once every
-// key_group appended tokens.
+// What bounds it: a prefill reads 512 B of fp16 per token and kv head and
+// writes a fraction of that, so HBM should (16384 tokens of 8 heads: 67 MB,
+// 14 us at the rate of a large copy); a single key group (decode) is bound
+// by its dependent memory round trips.  One workgroup of four waves takes
+// one (sequence, kv head, key group), reads every element once into
+// registers and packs there:
+//   - keys: a lane holds 8 consecutive channels of a token (16-byte loads,
+//     four tokens per wave and load).  These are the 8 elements of one matrix
+//     operand, so a row dword is one lane's codes, or the OR of two or four
+//     lanes 4 apart (DPP row shifts).  Minima and maxima run packed in fp16,
+//     across the lane rows by row swaps, across the waves through 2 KB of LDS.
+//   - values: wave w holds the 8 tokens of K-group w of a 32-token block, a
+//     lane two channels of each, which again are the 8 elements of one
+//     operand.  (min, -max) of a token travel as one packed pair; a butterfly
+//     over the 16 lanes leaves lane t with token t's pair, so a wave computes
+//     all its scales at once and row broadcasts hand them back.
+//   - the canonical layout keeps 8 channels per lane for both.
+// Codes need no division: see threshold() and quantize().  Measured, against one thread per channel with
+// fp64 quotients and bit-by-bit packing: 16384 tokens at K2V2 43 us (164 in
+// two launches), 131072 tokens at K1V1 175 us or 3.4 TB/s (1034), the key
+// group of a decode step 9 us (42); the vector instructions take about half
+// of the 16384-token launch (670 per wave), its ramp and tail the rest.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
+#include "decode_common.h"
 #include "kvq_internal.h"
 #include "kvq_layout.h"
 
 namespace kvq {
 namespace {
 
-__device__ __forceinline__ double half_bits_to_double(uint16_t h) {
-  return (double)__builtin_bit_cast(_Float16, h);
+typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ h2_t u2h(uint32_t v) { return __builtin_bit_cast(h2_t, v); }
+__device__ __forceinline__ uint32_t h2u(h2_t v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ float lo_f(uint32_t v) { return (float)u2h(v).x; }
+__device__ __forceinline__ float hi_f(uint32_t v) { return (float)u2h(v).y; }
+// Packed fp16 minimum and maximum as one instruction (the builtins quiet each
+// operand first; a NaN is found by probe_nan, whatever these return for it).
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+  uint32_t r;
+  asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+  uint32_t r;
+  asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+constexpr int kRowShl4 = 0x104, kRowShl8 = 0x108, kRowRor4 = 0x124, kRowRor8 = 0x128, kRowBcast = 0x150;
+
+// The value of the lane 16 (or 32) away joined with the own one by OP.
+template <typename OP>
+__device__ __forceinline__ uint32_t join16(uint32_t v, OP op) {
+  const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return op((uint32_t)s[0], (uint32_t)s[1]);
+}
+template <typename OP>
+__device__ __forceinline__ uint32_t join32(uint32_t v, OP op) {
+  const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return op((uint32_t)s[0], (uint32_t)s[1]);
 }
 
-// Smallest fp16 (bit pattern) whose value is >= s, for 0 <= s <= 65504.
-// Start from a rounded conversion and walk to the exact answer: positive fp16
-// patterns increase with their value, and the conversion is within an ulp.
-__device__ __forceinline__ bool half_ceil(double s, uint16_t& out) {
-  if (!(s <= 65504.0) || !(s >= 0.0)) return false;
-  if (s == 0.0) { out = 0; return true; }
-  uint16_t b = __builtin_bit_cast(uint16_t, (_Float16)(float)s);
-  while (half_bits_to_double(b) < s) ++b;
-  while (b > 1 && half_bits_to_double((uint16_t)(b - 1)) >= s) --b;
-  out = b;
-  return true;
+// A packed maximum that turns to +inf where the NaN probe (a sum of 0 * x)
+// says that the group holds a NaN or an infinity: no finite scale then.
+__device__ __forceinline__ uint32_t spoil(uint32_t mx, uint32_t probe) {
+  if (__builtin_isnan((float)u2h(probe).x)) mx = (mx & 0xFFFF0000u) | 0x7C00u;
+  if (__builtin_isnan((float)u2h(probe).y)) mx = (mx & 0x0000FFFFu) | 0x7C000000u;
+  return mx;
+}
+// Non-finite halves of x as 0 (in groups that got no finite scale).
+__device__ __forceinline__ uint32_t finite_or_zero(uint32_t x) {
+  if ((x & 0x7C00u) == 0x7C00u) x &= 0xFFFF0000u;
+  if ((x & 0x7C000000u) == 0x7C000000u) x &= 0x0000FFFFu;
+  return x;
+}
+__device__ __forceinline__ bool has_nan(uint32_t probe) {
+  return __builtin_isnan((float)u2h(probe).x) || __builtin_isnan((float)u2h(probe).y);
+}
+__device__ __forceinline__ uint32_t probe_nan(uint32_t x, uint32_t acc) {
+  return h2u(__builtin_elementwise_fma(u2h(x), (h2_t){(_Float16)0.f, (_Float16)0.f}, u2h(acc)));
 }
 
 __device__ __forceinline__ void raise_range(uint8_t* arena) {
   *reinterpret_cast<volatile uint32_t*>(arena) = 4u;  // KVQ_ERR_RANGE
 }
 
-__device__ __forceinline__ const uint16_t* token_row(const AppendArgs& a, const AppendSeq& S,
-                                                     const uint8_t* blk, uint32_t ring,
-                                                     const uint16_t* in, int h, int p) {
-  if (p < S.L_old) return reinterpret_cast<const uint16_t*>(blk + ring) + (size_t)(p % a.W) * kHeadDim;
-  return in + (((size_t)S.seq * a.n_max + (p - S.L_old)) * a.hkv + h) * kHeadDim;
+// Scale (low half) and zero-point (high half) of a group: the smallest fp16
+// s with s * (2^B - 1) >= max - min.  The range and the products are exact
+// in fp64, so the step from a rounded guess ends at the exact answer
+// (positive fp16 patterns increase with their value).  A group without a
+// finite scale gets the NaN pattern 0x7E00 and raises the range flag.
+template <int B>
+__device__ __forceinline__ uint32_t scale_zero(uint8_t* arena, float mn, float mx) {
+  if (mn == 0.f) mn = 0.f;  // +0 zero-point
+  const uint32_t zb = __builtin_bit_cast(uint16_t, (_Float16)mn);
+  constexpr double n = (double)((1 << B) - 1);
+  const double range = (double)mx - (double)mn;
+  if (!(range <= 65504.0 * n)) {
+    raise_range(arena);
+    return 0x7E00u | (zb << 16);
+  }
+  uint32_t b = 0u;
+  if (range > 0.0) {
+    // the guess is a neighbour of the quotient: one step at most is missing
+    b = min((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)((float)range * (float)(1.0 / n))), 0x7BFFu);
+    const uint32_t below = b > 0u ? b - 1u : 0u;
+    if ((double)__builtin_bit_cast(_Float16, (uint16_t)b) * n < range) b += 1u;
+    else if ((double)__builtin_bit_cast(_Float16, (uint16_t)below) * n >= range) b = below;
+  }
+  return b | (zb << 16);
 }
 
-// Pack `rows` rows of 128 codes (LDS, row-major) at `bits` bits into dwords.
-__device__ __forceinline__ void pack_rows(const uint8_t* codes, int rows, int bits, uint8_t* dst) {
-  const int dw_per_row = 4 * bits, per_dw = 32 / bits;
-  for (int k = threadIdx.x; k < rows * dw_per_row; k += blockDim.x) {
-    const int i = k / dw_per_row, w = k % dw_per_row;
-    uint32_t v = 0;
-    for (int e = 0; e < per_dw; ++e) v |= (uint32_t)codes[i * kHeadDim + w * per_dw + e] << (e * bits);
-    reinterpret_cast<uint32_t*>(dst + (size_t)i * 16 * bits)[w] = v;
+// One- and two-bit codes compare the fp16 input with the code's thresholds:
+// code > k iff x > T_k, T_k the largest fp16 below the boundary z + (k + 1/2) s
+// (an x on the boundary rounds to the even code: it stays at k for even k and
+// moves up for odd k).  The boundary is exact in fp64, and the sign of the
+// fp16 difference T_k - x is exact, two elements at a time.  Groups of one
+// value, or without a finite scale, get T_k = +inf: code 0.
+constexpr uint32_t kInf16 = 0x7C00u;
+template <int K>
+__device__ __forceinline__ uint32_t threshold(uint32_t sz) {
+  const uint32_t sb = sz & 0xFFFFu;
+  if (sb == 0u || sb == 0x7E00u) return kInf16;
+  const double b = (double)lo_f(sz) * (K + 0.5) + (double)hi_f(sz);
+  const _Float16 t = (_Float16)(float)b;  // a neighbour of b: above it, one step down
+  uint32_t u = __builtin_bit_cast(uint16_t, t);
+  const bool above = (K & 1) ? (double)t >= b : (double)t > b;
+  if (above) u = (u & 0x7FFFu) == 0u ? 0x8001u : (u & 0x8000u) ? u + 1u : u - 1u;
+  return u;
+}
+template <int B>
+struct Thresholds {  // both halves of t[k] hold T_k (values), or two channels' T_k (keys)
+  uint32_t t[B == 1 ? 1 : 3];
+};
+// Bits 15 and 31 of p[i] are code bit i of the two elements of x.
+template <int B>
+__device__ __forceinline__ void code_bits(uint32_t x, const Thresholds<B>& T, uint32_t (&p)[B]) {
+  if constexpr (B == 1) {
+    p[0] = h2u(u2h(T.t[0]) - u2h(x));
+  } else {
+    const uint32_t u0 = h2u(u2h(T.t[0]) - u2h(x)), u1 = h2u(u2h(T.t[1]) - u2h(x)), u2 = h2u(u2h(T.t[2]) - u2h(x));
+    p[0] = u0 ^ u1 ^ u2;
+    p[1] = u1;
+  }
+}
+// Code bits moved to bit `at` (+ the code bit) of each half of acc.
+template <int B>
+__device__ __forceinline__ void add_codes(uint32_t x, const Thresholds<B>& T, int at, uint32_t& acc) {
+  uint32_t p[B];
+  code_bits<B>(x, T, p);
+#pragma unroll
+  for (int i = 0; i < B; ++i) acc |= (p[i] >> (15 - at - i)) & (0x00010001u << (at + i));
+}
+
+// fp32 scale, its reciprocal (an estimate) and zero-point of a group.  A
+// group without a finite scale gets s = inf: every code 0.
+struct Grid {
+  float s, rs, z;
+};
+__device__ __forceinline__ Grid grid_of(uint32_t sz) {
+  const bool bad = (sz & 0xFFFFu) == 0x7E00u;
+  Grid g;
+  g.s = bad ? __builtin_inff() : lo_f(sz);
+  g.rs = (sz & 0xFFFFu) != 0u && !bad ? __builtin_amdgcn_rcpf(g.s) : 0.f;
+  g.z = bad ? 0.f : hi_f(sz);
+  return g;
+}
+
+// code = round-half-even((x - z) / s), exactly, without a division.  With
+// f = floor of the estimated quotient, the code is f or f + 1 (an estimate
+// off by an ulp next to an integer moves f, not the result): r, the sign of
+// x - z - (f + 1/2) s, decides.  d = fl(x - z) and (f + 1/2) s (at most 20
+// bits) enter one fma, whose sign is exact for d; the rest d_lo = (x - z) - d
+// is below half an ulp of d while any nonzero r is at least an ulp of d (the
+// product is a multiple of 2^-19 d), so d_lo matters only when r = 0, as does
+// the tie to the even code.
+template <int B>
+__device__ __forceinline__ uint32_t quantize(float x, const Grid& g) {
+  const float d = x - g.z;
+  const float f = __builtin_floorf(d * g.rs);
+  const float r = fmaf(-(f + 0.5f), g.s, d);
+  bool up = r > 0.f;
+  const uint32_t fi = (uint32_t)f;
+  if (__builtin_amdgcn_ballot_w64(r == 0.f)) {
+    const float zp = d - x, xp = d - zp, dlo = (x - xp) + (-g.z - zp);  // exact rest of x - z
+    if (r == 0.f) up = dlo > 0.f || (dlo == 0.f && (fi & 1u));
+  }
+  return fi + (up ? 1u : 0u);
+}
+
+// 8 halves of a row at p: one 16-byte load, or halves (inputs that are not
+// 16-byte aligned).
+template <bool AL>
+__device__ __forceinline__ u4_t load8(const uint16_t* p) {
+  if constexpr (AL) return *reinterpret_cast<const u4_t*>(p);
+  u4_t v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = (uint32_t)p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
+  return v;
+}
+template <bool AL>
+__device__ __forceinline__ uint32_t load2(const uint16_t* p) {
+  if constexpr (AL) return *reinterpret_cast<const uint32_t*>(p);
+  return (uint32_t)p[0] | ((uint32_t)p[1] << 16);
+}
+
+// Row of token p: in the ring (appended by an earlier call) or in the input.
+struct Rows {
+  const uint16_t* in;    // input row of token L_old of this head
+  const uint16_t* ring;
+  size_t stride;         // halves from one input token to the next
+  int L_old, W;
+  bool fresh;            // none of the group's tokens sits in the ring (uniform)
+  __device__ __forceinline__ const uint16_t* at(int p) const {
+    if (!fresh && p < L_old) return ring + (size_t)(p % W) * kHeadDim;
+    return in + (size_t)(p - L_old) * stride;
+  }
+};
+
+// Eight codes of consecutive channels as B bytes of a canonical row (4 and 8
+// bits; one and two bits: even channels' codes at 2*B*i of the low half of
+// acc, odd ones' of the high half).
+template <int B>
+__device__ __forceinline__ void store8(const uint32_t (&c)[8], uint8_t* rowp, int cc) {
+  uint32_t lo = 0u, hi = 0u;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if (B < 8 || e < 4) lo |= c[e] << (B * e);
+    else hi |= c[e] << (8 * (e - 4));
+  }
+  if constexpr (B == 4) reinterpret_cast<uint32_t*>(rowp)[cc] = lo;
+  else reinterpret_cast<uint2*>(rowp)[cc] = make_uint2(lo, hi);
+}
+template <int B>
+__device__ __forceinline__ void store_row_bits(uint32_t acc, uint8_t* rowp, int cc) {
+  const uint32_t v = (acc & 0xFFFFu) | (acc >> (16 - B));
+  if constexpr (B == 1) rowp[cc] = (uint8_t)v;
+  else reinterpret_cast<uint16_t*>(rowp)[cc] = (uint16_t)v;
+}
+
+// The lane's part of its key row dwords (matrix layout, kvq_layout.h: key_bit)
+// into the row at o: operand block kb, lane group g4.
+template <int B>
+__device__ __forceinline__ void store_key_words(const uint32_t (&w)[2], int kb, int g4, uint32_t* o) {
+  if constexpr (B == 1) {  // dword g4: the four blocks kb, lanes 4 apart
+    uint32_t v = w[0] << (4 * kb);
+    v |= dpp<kRowShl4>(v);
+    v |= dpp<kRowShl8>(v);
+    if (kb == 0) o[g4] = v;
+  } else if constexpr (B == 2) {  // dword 2*g4 + (kb >> 1): two blocks
+    uint32_t v = w[0] << (8 * (kb & 1));
+    v |= dpp<kRowShl4>(v);
+    if ((kb & 1) == 0) o[2 * g4 + (kb >> 1)] = v;
+  } else if constexpr (B == 4) {
+    o[4 * g4 + kb] = w[0];
+  } else {
+    *reinterpret_cast<uint2*>(o + 8 * g4 + 2 * kb) = make_uint2(w[0], w[1]);
   }
 }
 
-// Matrix layout (kvq_layout.h), key rows: each bit of a row dword comes from
-// the channel and code bit key_bit_owner names.
-__device__ __forceinline__ void pack_key_rows_matrix(const uint8_t* codes, int rows, int bits, uint8_t* dst) {
-  const int dw_per_row = 4 * bits;
-  for (int k = threadIdx.x; k < rows * dw_per_row; k += blockDim.x) {
-    const int i = k / dw_per_row, w = k % dw_per_row;
-    uint32_t v = 0;
-    for (int q = 0; q < 32; ++q) {
-      int c, p;
-      key_bit_owner(w, q, bits, c, p);
-      v |= (uint32_t)((codes[i * kHeadDim + c] >> p) & 1u) << q;
+// Keys of one group, second half: codes of the lane's 8 channels of the
+// tokens t = 16*i + 4*wv + row, written in either layout.  par: per channel,
+// the thresholds [k][128] (fp16) at one and two bits, (scale, zero) else.
+template <int B, int GK>
+__device__ __forceinline__ void key_codes(const u4_t (&x)[GK / 16], const uint32_t* par, bool matrix, uint8_t* dst,
+                                          int lane, int wv) {
+  const int cc = lane & 15, row = lane >> 4, kb = cc >> 2, g4 = cc & 3;
+  if constexpr (B <= 2) {
+    constexpr int NT = B == 1 ? 1 : 3;
+    u4_t tk[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) tk[k] = *reinterpret_cast<const u4_t*>(par + 64 * k + 4 * cc);
+#pragma unroll
+    for (int i = 0; i < GK / 16; ++i) {
+      uint8_t* rowp = dst + (size_t)(16 * i + 4 * wv + row) * 16 * B;
+      uint32_t acc = 0u;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        Thresholds<B> T;
+#pragma unroll
+        for (int k = 0; k < NT; ++k) T.t[k] = tk[k][m];
+        // matrix: pair m at bits B*m and 16 + B*m; rows: even channels at
+        // 2*B*m of the low half, odd ones of the high half
+        if (matrix) add_codes<B>(x[i][m], T, B * m, acc);
+        else add_codes<B>(x[i][m], T, 2 * B * m, acc);
+      }
+      if (matrix) {
+        const uint32_t w[2] = {acc, 0u};
+        store_key_words<B>(w, kb, g4, reinterpret_cast<uint32_t*>(rowp));
+      } else {
+        store_row_bits<B>(acc, rowp, cc);
+      }
     }
-    reinterpret_cast<uint32_t*>(dst + (size_t)i * 16 * bits)[w] = v;
-  }
-}
-
-// Matrix layout, value codes: 32-token blocks of 512*b bytes in MFMA lane order.
-__device__ __forceinline__ void pack_value_blocks_matrix(const uint8_t* codes, int rows, int bits, uint8_t* dst) {
-  const int dw_per_block = 128 * bits;
-  for (int k = threadIdx.x; k < (rows / 32) * dw_per_block; k += blockDim.x) {
-    const int blk = k / dw_per_block, w = k % dw_per_block;
-    uint32_t v = 0;
-    for (int q = 0; q < 32; ++q) {
-      int r, c, p;
-      value_bit_owner(w, q, bits, r, c, p);
-      v |= (uint32_t)((codes[(blk * 32 + r) * kHeadDim + c] >> p) & 1u) << q;
+  } else {
+    Grid g[8];
+    const u4_t a = *reinterpret_cast<const u4_t*>(par + 8 * cc), b = *reinterpret_cast<const u4_t*>(par + 8 * cc + 4);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[e] = grid_of(e < 4 ? a[e] : b[e - 4]);
+#pragma unroll
+    for (int i = 0; i < GK / 16; ++i) {
+      uint32_t c[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) c[e] = quantize<B>(e & 1 ? hi_f(x[i][e >> 1]) : lo_f(x[i][e >> 1]), g[e]);
+      uint8_t* rowp = dst + (size_t)(16 * i + 4 * wv + row) * 16 * B;
+      if (matrix) {
+        uint32_t w[2] = {0u, 0u};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if constexpr (B == 8) w[e >> 2] |= c[e] << (8 * (e & 3));
+          else w[0] |= c[e] << (B * (e >> 1) + 16 * (e & 1));
+        }
+        store_key_words<B>(w, kb, g4, reinterpret_cast<uint32_t*>(rowp));
+      } else {
+        store8<B>(c, rowp, cc);
+      }
     }
-    reinterpret_cast<uint32_t*>(dst + (size_t)blk * 512 * bits)[w] = v;
   }
 }
 
-__device__ void quantize_group(const AppendArgs& a, const AppendSeq& S, int h, int gi, int bk,
-                               int bv, uint8_t* codes, uint32_t* vmax) {
+// (min, -max) of the two halves of x in one packed pair: minima alone join
+// two such pairs.
+__device__ __forceinline__ uint32_t min_negmax(uint32_t x) {
+  const uint32_t l2 = __builtin_amdgcn_perm(0u, x, 0x01000100u) ^ 0x80000000u;
+  const uint32_t h2 = __builtin_amdgcn_perm(0u, x, 0x03020302u) ^ 0x80000000u;
+  return pk_min(l2, h2);
+}
+
+// f(std::integral_constant<int, t>) for the 8 tokens of a lane.
+template <typename F>
+__device__ __forceinline__ void for_tokens(F f) {
+  f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{});
+  f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
+  f(std::integral_constant<int, 4>{}); f(std::integral_constant<int, 5>{});
+  f(std::integral_constant<int, 6>{}); f(std::integral_constant<int, 7>{});
+}
+
+// Values of one 32-token block, matrix layout: wave wv = K-group, lane =
+// channels 2*lane, 2*lane + 1, x[t] = token value_token(wv, t).  Returns the
+// wave's largest scale (fp16 bits).
+template <int B>
+__device__ __forceinline__ uint32_t value_block_matrix(uint8_t* arena, uint32_t (&x)[8], int gv, uint8_t* vcb,
+                                                       uint8_t* vmb, int lane, int wv) {
+  uint32_t m[8], nan = 0u;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    m[t] = min_negmax(x[t]);
+    nan = probe_nan(x[t], nan);
+  }
+  if (__builtin_amdgcn_ballot_w64(has_nan(nan))) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (finite_or_zero(x[t]) != x[t]) {
+        m[t] = 0xFC007C00u;  // range +inf
+        x[t] = finite_or_zero(x[t]);
+      }
+  }
+  // butterfly over the 16 lanes of a row: lane ends with token (lane & 7)
+  const bool b0 = lane & 1, b1 = lane & 2;
+  uint32_t n[4], o[2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    n[j] = pk_min(b0 ? m[2 * j + 1] : m[2 * j], dpp<dec::kQuadXor1>(b0 ? m[2 * j] : m[2 * j + 1]));
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    o[j] = pk_min(b1 ? n[2 * j + 1] : n[2 * j], dpp<dec::kQuadXor2>(b1 ? n[2 * j] : n[2 * j + 1]));
+    o[j] = pk_min(o[j], dpp<kRowRor4>(o[j]));
+    o[j] = pk_min(o[j], dpp<kRowRor8>(o[j]));
+  }
+  uint32_t v = (lane & 4) ? o[1] : o[0];
+  if (gv >= 64) v = join16(v, pk_min);
+  if (gv >= 128) v = join32(v, pk_min);
+  const uint32_t sz = scale_zero<B>(arena, lo_f(v), -hi_f(v));
+  const int row = lane >> 4, rpg = gv / 32, ng = kHeadDim / gv;
+  if ((lane & 15) < 8 && (row & (rpg - 1)) == 0) {
+    const int at = (row / rpg) * 32 + 8 * wv + (lane & 7);  // value_meta_s / value_meta_z
+    reinterpret_cast<uint16_t*>(vmb)[at] = (uint16_t)sz;
+    reinterpret_cast<uint16_t*>(vmb)[ng * 32 + at] = (uint16_t)(sz >> 16);
+  }
+  // codes of the two channels, element t of their operand words w0, w1
+  uint32_t w0[2] = {0u, 0u}, w1[2] = {0u, 0u};
+  if constexpr (B <= 2) {
+    Thresholds<B> own;
+    own.t[0] = threshold<0>(sz) * 0x10001u;
+    if constexpr (B == 2) {
+      own.t[1] = threshold<1>(sz) * 0x10001u;
+      own.t[2] = threshold<2>(sz) * 0x10001u;
+    }
+    uint32_t acc = 0u;  // low half: the even channel, high half: the odd one
+    for_tokens([&](auto tc) {
+      constexpr int t = decltype(tc)::value;
+      Thresholds<B> T;
+#pragma unroll
+      for (int k = 0; k < (B == 1 ? 1 : 3); ++k) T.t[k] = dpp<kRowBcast + t>(own.t[k]);
+      add_codes<B>(x[t], T, B == 1 ? (t >> 1) + 4 * (t & 1) : 2 * t, acc);
+    });
+    if constexpr (B == 1) {  // pairs apart: elements 2i at bit i, 2i + 1 at bit 16 + i
+      w0[0] = (acc & 0xFu) | ((acc & 0xF0u) << 12);
+      w1[0] = ((acc >> 16) & 0xFu) | ((acc >> 4) & 0xF0000u);
+    } else {
+      w0[0] = acc & 0xFFFFu;
+      w1[0] = acc >> 16;
+    }
+  } else {
+    for_tokens([&](auto tc) {
+      constexpr int t = decltype(tc)::value;
+      const Grid g = grid_of(dpp<kRowBcast + t>(sz));
+      constexpr int sh = B == 4 ? 4 * (t >> 1) + 16 * (t & 1) : 8 * (t & 3);
+      w0[B == 8 ? t >> 2 : 0] |= quantize<B>(lo_f(x[t]), g) << sh;
+      w1[B == 8 ? t >> 2 : 0] |= quantize<B>(hi_f(x[t]), g) << sh;
+    });
+  }
+  const int mb = lane >> 3, c16 = 2 * (lane & 7);
+  uint32_t* o32 = reinterpret_cast<uint32_t*>(vcb);
+  auto bit_or = [](uint32_t p, uint32_t q) { return p | q; };
+  if constexpr (B <= 2) {
+    // operands that share a dword sit in lanes 8 (and 16) apart; of the
+    // lanes that then hold the same word, one stores the even channel and
+    // one the odd
+    w0[0] <<= B == 1 ? 4 * (mb & 3) : 16 * (mb & 1);
+    w1[0] <<= B == 1 ? 4 * (mb & 3) : 16 * (mb & 1);
+    w0[0] |= dpp<kRowRor8>(w0[0]);
+    w1[0] |= dpp<kRowRor8>(w1[0]);
+    uint32_t w = (mb & 1) ? w1[0] : w0[0];
+    const int L = c16 + (mb & 1) + 16 * wv;
+    if constexpr (B == 1) {
+      w = join16(w, bit_or);
+      if ((lane & 16) == 0) o32[L * 2 + (mb >> 2)] = w;
+    } else {
+      o32[L * 4 + (mb >> 1)] = w;
+    }
+  } else if constexpr (B == 4) {
+    o32[(c16 + 16 * wv) * 8 + mb] = w0[0];
+    o32[(c16 + 1 + 16 * wv) * 8 + mb] = w1[0];
+  } else {
+    *reinterpret_cast<uint2*>(o32 + (c16 + 16 * wv) * 16 + 2 * mb) = make_uint2(w0[0], w0[1]);
+    *reinterpret_cast<uint2*>(o32 + (c16 + 1 + 16 * wv) * 16 + 2 * mb) = make_uint2(w1[0], w1[1]);
+  }
+  const uint32_t s = sz & 0xFFFFu;
+  return s == 0x7E00u ? 0u : s;
+}
+
+// Values of one 32-token block, canonical layout: lane = channels 8*cc ..
+// 8*cc + 7 of the tokens t = 16*i + 4*wv + row.  vmb: the block's first meta.
+template <int B>
+__device__ __forceinline__ uint32_t value_block_rows(uint8_t* arena, u4_t (&x)[2], int gv, uint8_t* vcb,
+                                                     uint32_t* vmb, int lane, int wv) {
+  const int cc = lane & 15, row = lane >> 4, lpg = gv / 8, ng = kHeadDim / gv;
+  uint32_t most = 0u;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    uint32_t nan = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) nan = probe_nan(x[i][k], nan);
+    uint32_t v = min_negmax(x[i][0]);
+#pragma unroll
+    for (int k = 1; k < 4; ++k) v = pk_min(v, min_negmax(x[i][k]));
+    if (__builtin_amdgcn_ballot_w64(has_nan(nan)) && has_nan(nan)) {
+      v = 0xFC007C00u;  // range +inf
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[i][k] = finite_or_zero(x[i][k]);
+    }
+    if (lpg >= 2) v = pk_min(v, dpp<dec::kQuadXor1>(v));
+    if (lpg >= 4) v = pk_min(v, dpp<dec::kQuadXor2>(v));
+    if (lpg >= 8) v = pk_min(v, dpp<dec::kHalfMirror>(v));
+    if (lpg >= 16) v = pk_min(v, dpp<dec::kMirror>(v));
+    const uint32_t sz = scale_zero<B>(arena, lo_f(v), -hi_f(v));
+    const int t = 16 * i + 4 * wv + row;
+    if ((cc & (lpg - 1)) == 0) vmb[(size_t)t * ng + cc / lpg] = sz;
+    if constexpr (B <= 2) {
+      Thresholds<B> T;
+      T.t[0] = threshold<0>(sz) * 0x10001u;
+      if constexpr (B == 2) {
+        T.t[1] = threshold<1>(sz) * 0x10001u;
+        T.t[2] = threshold<2>(sz) * 0x10001u;
+      }
+      uint32_t acc = 0u;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) add_codes<B>(x[i][m], T, 2 * B * m, acc);
+      store_row_bits<B>(acc, vcb + (size_t)t * 16 * B, cc);
+    } else {
+      const Grid g = grid_of(sz);
+      uint32_t c[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) c[e] = quantize<B>(e & 1 ? hi_f(x[i][e >> 1]) : lo_f(x[i][e >> 1]), g);
+      store8<B>(c, vcb + (size_t)t * 16 * B, cc);
+    }
+    const uint32_t s = sz & 0xFFFFu;
+    most = max(most, s == 0x7E00u ? 0u : s);
+  }
+  return most;
+}
+
+template <int GK, bool AL>
+__device__ __forceinline__ void quantize_group(const AppendArgs& a, const AppendSeq& S, int h, int gi, int bk, int bv,
+                                               uint32_t* minmax, uint32_t* par) {
   uint8_t* blk = a.arena + S.head0 + (uint64_t)h * a.head_stride;  // the fp16 ring's region
-  const int gk = a.gk, j = S.Lq_old / gk + gi, p0 = j * gk;
-  const int c = threadIdx.x;
+  const int p0 = S.Lq_old + gi * GK;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cc = lane & 15, row = lane >> 4;
+  const size_t in0 = ((size_t)S.seq * a.n_max * a.hkv + h) * kHeadDim;
+  const Rows rk{a.K + in0, reinterpret_cast<const uint16_t*>(blk + a.tk), (size_t)a.hkv * kHeadDim, S.L_old, a.W, p0 >= S.L_old};
+  const Rows rv{a.V + in0, reinterpret_cast<const uint16_t*>(blk + a.tv), (size_t)a.hkv * kHeadDim, S.L_old, a.W, p0 >= S.L_old};
+
+  u4_t kx[GK / 16];
+#pragma unroll
+  for (int i = 0; i < GK / 16; ++i) kx[i] = load8<AL>(rk.at(p0 + 16 * i + 4 * wv + row) + 8 * cc);
+  uint32_t vx[8];
+  u4_t vr[2];
+  auto load_v = [&](int b) {
+    if (a.matrix) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) vx[t] = load2<AL>(rv.at(p0 + 32 * b + value_token(wv, t)) + 2 * lane);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) vr[i] = load8<AL>(rv.at(p0 + 32 * b + 16 * i + 4 * wv + row) + 8 * cc);
+    }
+  };
+  load_v(0);
+  uint32_t* bound = reinterpret_cast<uint32_t*>(blk + a.vb);
+  const uint32_t seen = __hip_atomic_load(bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // the packed segment (head region or page) of the group, and the group's
-  // first token and index in it
+  // first token in it
   int t0;
   uint8_t* seg = a.arena + packed_seg(a.pm, S.head0, a.head_stride, S.seq, h, p0, t0);
-  const int jj = t0 / gk;
 
-  // keys: thread c owns channel c of the group's gk tokens
+  // minima and maxima of the lane's channel pairs over its tokens, then over
+  // the lane rows; the waves' results meet in LDS
   {
-    double mn = __builtin_inf(), mx = -__builtin_inf();
-    bool finite = true;
-    for (int i = 0; i < gk; ++i) {
-      const double v = half_bits_to_double(token_row(a, S, blk, a.tk, a.K, h, p0 + i)[c]);
-      finite &= __builtin_isfinite(v);
-      mn = v < mn ? v : mn;
-      mx = v > mx ? v : mx;
+    u4_t mn = kx[0], mx = kx[0], nan = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < GK / 16; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (i > 0) {
+          mn[k] = pk_min(mn[k], kx[i][k]);
+          mx[k] = pk_max(mx[k], kx[i][k]);
+        }
+        nan[k] = probe_nan(kx[i][k], nan[k]);
+      }
+    if (__builtin_amdgcn_ballot_w64(has_nan(nan[0]) || has_nan(nan[1]) || has_nan(nan[2]) || has_nan(nan[3]))) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        mx[k] = spoil(mx[k], nan[k]);
+#pragma unroll
+        for (int i = 0; i < GK / 16; ++i) kx[i][k] = finite_or_zero(kx[i][k]);
+      }
     }
-    if (mn == 0.0) mn = 0.0;  // +0 zero-point
-    uint16_t sb = 0;
-    const bool ok = finite && half_ceil((mx - mn) / (double)((1 << bk) - 1), sb);
-    if (!ok) { raise_range(a.arena); sb = 0x7E00; }
-    const double sv = half_bits_to_double(sb);
-    for (int i = 0; i < gk; ++i) {
-      const double v = half_bits_to_double(token_row(a, S, blk, a.tk, a.K, h, p0 + i)[c]);
-      codes[i * kHeadDim + c] = (ok && sv != 0.0) ? (uint8_t)__builtin_rint((v - mn) / sv) : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      mn[k] = join32(join16(mn[k], pk_min), pk_min);
+      mx[k] = join32(join16(mx[k], pk_max), pk_max);
     }
-    uint16_t* km = reinterpret_cast<uint16_t*>(seg + a.km) + (size_t)jj * 2 * kHeadDim;
-    km[c] = sb;
-    km[kHeadDim + c] = __builtin_bit_cast(uint16_t, (_Float16)mn);
+    if (row == 0) {
+      *reinterpret_cast<u4_t*>(minmax + wv * 128 + 4 * cc) = mn;
+      *reinterpret_cast<u4_t*>(minmax + wv * 128 + 64 + 4 * cc) = mx;
+    }
   }
   __syncthreads();
-  if (a.matrix)
-    pack_key_rows_matrix(codes, gk, bk, seg + a.kc + (size_t)t0 * 16 * bk);
-  else
-    pack_rows(codes, gk, bk, seg + a.kc + (size_t)t0 * 16 * bk);
-  __syncthreads();
+  if (threadIdx.x < kHeadDim) {
+    const int c = threadIdx.x;
+    const uint16_t* mm = reinterpret_cast<const uint16_t*>(minmax);
+    float mn = __builtin_inff(), mx = -__builtin_inff();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      mn = fminf(mn, (float)__builtin_bit_cast(_Float16, mm[w * 256 + c]));
+      mx = fmaxf(mx, (float)__builtin_bit_cast(_Float16, mm[w * 256 + 128 + c]));
+    }
+    uint16_t* t16 = reinterpret_cast<uint16_t*>(par);
+    uint32_t v;
+    switch (bk) {
+      case 1:
+        v = scale_zero<1>(a.arena, mn, mx);
+        t16[c] = (uint16_t)threshold<0>(v);
+        break;
+      case 2:
+        v = scale_zero<2>(a.arena, mn, mx);
+        t16[c] = (uint16_t)threshold<0>(v);
+        t16[128 + c] = (uint16_t)threshold<1>(v);
+        t16[256 + c] = (uint16_t)threshold<2>(v);
+        break;
+      case 4: par[c] = v = scale_zero<4>(a.arena, mn, mx); break;
+      default: par[c] = v = scale_zero<8>(a.arena, mn, mx); break;
+    }
+    uint16_t* km = reinterpret_cast<uint16_t*>(seg + a.km) + (size_t)(t0 / GK) * 2 * kHeadDim;
+    km[c] = (uint16_t)v;
+    km[kHeadDim + c] = (uint16_t)(v >> 16);
+  }
 
-  // values: one item per (token, value group); the largest value scale of
-  // the group raises the head's bound (decode sizes its weight shift by it)
-  if (threadIdx.x == 0) *vmax = 0u;
-  __syncthreads();
+  // values: they need no other wave, and overlap the keys' scales
   const int ng = kHeadDim / a.gv;
-  for (int it = threadIdx.x; it < gk * ng; it += blockDim.x) {
-    const int i = it / ng, g = it % ng;
-    const uint16_t* row = token_row(a, S, blk, a.tv, a.V, h, p0 + i) + g * a.gv;
-    double mn = __builtin_inf(), mx = -__builtin_inf();
-    bool finite = true;
-    for (int e = 0; e < a.gv; ++e) {
-      const double v = half_bits_to_double(row[e]);
-      finite &= __builtin_isfinite(v);
-      mn = v < mn ? v : mn;
-      mx = v > mx ? v : mx;
-    }
-    if (mn == 0.0) mn = 0.0;
-    uint16_t sb = 0;
-    const bool ok = finite && half_ceil((mx - mn) / (double)((1 << bv) - 1), sb);
-    if (!ok) { raise_range(a.arena); sb = 0x7E00; }
-    else atomicMax(vmax, (uint32_t)sb);  // positive fp16 patterns order like their values
-    const double sv = half_bits_to_double(sb);
-    for (int e = 0; e < a.gv; ++e) {
-      const double v = half_bits_to_double(row[e]);
-      codes[i * kHeadDim + g * a.gv + e] = (ok && sv != 0.0) ? (uint8_t)__builtin_rint((v - mn) / sv) : 0;
-    }
-    const uint32_t zb = __builtin_bit_cast(uint16_t, (_Float16)mn);
+  uint32_t most = 0u;
+  for (int b = 0; b < GK / 32; ++b) {
+    if (b > 0) load_v(b);
+    uint8_t* vcb = seg + a.vc + (size_t)(t0 + 32 * b) * 16 * bv;
+    uint8_t* vmb = seg + a.vm + (size_t)(t0 + 32 * b) * 4 * ng;
+    uint32_t s = 0u;
     if (a.matrix) {
-      uint8_t* vmb = seg + a.vm + (size_t)((t0 + i) / 32) * 128 * ng;
-      const int r = (t0 + i) % 32;
-      *reinterpret_cast<uint16_t*>(vmb + value_meta_s(g, r)) = sb;
-      *reinterpret_cast<uint16_t*>(vmb + value_meta_z(g, r, ng)) = (uint16_t)zb;
+      switch (bv) {
+        case 1: s = value_block_matrix<1>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
+        case 2: s = value_block_matrix<2>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
+        case 4: s = value_block_matrix<4>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
+        default: s = value_block_matrix<8>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
+      }
     } else {
-      reinterpret_cast<uint32_t*>(seg + a.vm)[(size_t)(t0 + i) * ng + g] = (uint32_t)sb | (zb << 16);
+      uint32_t* vm32 = reinterpret_cast<uint32_t*>(vmb);
+      switch (bv) {
+        case 1: s = value_block_rows<1>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
+        case 2: s = value_block_rows<2>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
+        case 4: s = value_block_rows<4>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
+        default: s = value_block_rows<8>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
+      }
+    }
+    most = max(most, s);
+  }
+  // the largest value scale raises the head's bound (decode sizes its weight
+  // shift by it); the bound only grows, so a wave below a value seen earlier
+  // has nothing to add
+  if (__builtin_amdgcn_ballot_w64(most > seen)) {
+    for (int d = 32; d > 0; d >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d));
+    if (lane == 0) atomicMax(bound, most);
+  }
+
+  __syncthreads();
+  uint8_t* kdst = seg + a.kc + (size_t)t0 * 16 * bk;
+  switch (bk) {
+    case 1: key_codes<1, GK>(kx, par, a.matrix, kdst, lane, wv); break;
+    case 2: key_codes<2, GK>(kx, par, a.matrix, kdst, lane, wv); break;
+    case 4: key_codes<4, GK>(kx, par, a.matrix, kdst, lane, wv); break;
+    default: key_codes<8, GK>(kx, par, a.matrix, kdst, lane, wv); break;
+  }
+}
+
+// Copy part `part` (kCopyTokens tokens) of the new tokens that stay fp16 into
+// the ring of head h.
+template <bool AL>
+__device__ __forceinline__ void copy_ring(const AppendArgs& a, const AppendSeq& S, int h, int part) {
+  uint8_t* blk = a.arena + S.head0 + (uint64_t)h * a.head_stride;
+  const int first = max(S.Lq_new, S.L_old) + part * kCopyTokens, end = min(S.L_new, first + kCopyTokens);
+  const size_t in0 = ((size_t)S.seq * a.n_max * a.hkv + h) * kHeadDim;
+  constexpr int kPer = kCopyTokens * (kHeadDim / 8) / kAppendThreads;  // 16-byte pieces per thread and tensor
+  u4_t x[2][kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int idx = i * kAppendThreads + threadIdx.x, p = first + (idx >> 4);
+    if (p < end) {
+      const size_t src = in0 + (size_t)(p - S.L_old) * a.hkv * kHeadDim + (idx & 15) * 8;
+      x[0][i] = load8<AL>(a.K + src);
+      x[1][i] = load8<AL>(a.V + src);
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) atomicMax(reinterpret_cast<uint32_t*>(blk + a.vb), *vmax);
-  if (a.matrix)
-    pack_value_blocks_matrix(codes, gk, bv, seg + a.vc + (size_t)t0 * 16 * bv);
-  else
-    pack_rows(codes, gk, bv, seg + a.vc + (size_t)t0 * 16 * bv);
-}
-
-// Copy the new tokens that stay fp16 into the ring of head h.
-__device__ void copy_ring(const AppendArgs& a, const AppendSeq& S, int h) {
-  uint8_t* blk = a.arena + S.head0 + (uint64_t)h * a.head_stride;
-  uint16_t* rk = reinterpret_cast<uint16_t*>(blk + a.tk);
-  uint16_t* rv = reinterpret_cast<uint16_t*>(blk + a.tv);
-  const int first = S.Lq_new > S.L_old ? S.Lq_new : S.L_old;
-  const int c = threadIdx.x;
-  for (int p = first; p < S.L_new; ++p) {
-    const size_t src = (((size_t)S.seq * a.n_max + (p - S.L_old)) * a.hkv + h) * kHeadDim + c;
-    rk[(size_t)(p % a.W) * kHeadDim + c] = a.K[src];
-    rv[(size_t)(p % a.W) * kHeadDim + c] = a.V[src];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int idx = i * kAppendThreads + threadIdx.x, p = first + (idx >> 4);
+    if (p < end) {
+      const size_t dst = ((size_t)(p % a.W) * kHeadDim + (idx & 15) * 8) * 2;
+      *reinterpret_cast<u4_t*>(blk + a.tk + dst) = x[0][i];
+      *reinterpret_cast<u4_t*>(blk + a.tv + dst) = x[1][i];
+    }
   }
 }
 
-__global__ __launch_bounds__(128) void append_kernel(AppendArgs a, int bk, int bv) {
-  __shared__ uint8_t codes[128 * kHeadDim];
-  __shared__ uint32_t vmax;
+template <int GK, bool AL>
+__global__ __launch_bounds__(kAppendThreads) void append_kernel(AppendArgs a, int bk, int bv) {
+  __shared__ __attribute__((aligned(16))) uint32_t minmax[4 * 128], par[192];
   const int wg = blockIdx.x;
   int si = 0;
   for (int i = 1; i < a.nseq; ++i) si = (a.seq[i].wg_begin <= wg) ? i : si;
   const AppendSeq& S = a.seq[si];
-  const int local = wg - S.wg_begin;
-  const int nquant = a.quantize ? S.n_quant * a.hkv : 0;
-  if (local < nquant) {
-    quantize_group(a, S, local / S.n_quant, local % S.n_quant, bk, bv, codes, &vmax);
-  } else if (S.do_copy) {
-    copy_ring(a, S, local - nquant);
+  // kv heads fastest: neighbouring workgroups read neighbouring 256-byte rows
+  const int local = wg - S.wg_begin, part = local / a.hkv, h = local - part * a.hkv;
+  const int nquant = a.quantize ? S.n_quant : 0;
+  if (part < nquant) {
+    quantize_group<GK, AL>(a, S, h, part, bk, bv, minmax, par);
+  } else {
+    copy_ring<AL>(a, S, h, part - nquant);
   }
 }
 
@@ -223,7 +711,25 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* p, size_t n) {
 
 int launch_append(const AppendArgs& a, int bk, int bv, void* stream) {
   if (a.total_wg <= 0) return 0;
-  hipLaunchKernelGGL(append_kernel, dim3(a.total_wg), dim3(128), 0, (hipStream_t)stream, a, bk, bv);
+  // 16-byte input loads where both inputs allow them
+  const bool al = (reinterpret_cast<uintptr_t>(a.K) | reinterpret_cast<uintptr_t>(a.V)) % 16 == 0;
+  const dim3 grid(a.total_wg), block(kAppendThreads);
+  hipStream_t s = (hipStream_t)stream;
+  switch (a.gk) {
+    case 32:
+      if (al) hipLaunchKernelGGL((append_kernel<32, true>), grid, block, 0, s, a, bk, bv);
+      else hipLaunchKernelGGL((append_kernel<32, false>), grid, block, 0, s, a, bk, bv);
+      break;
+    case 64:
+      if (al) hipLaunchKernelGGL((append_kernel<64, true>), grid, block, 0, s, a, bk, bv);
+      else hipLaunchKernelGGL((append_kernel<64, false>), grid, block, 0, s, a, bk, bv);
+      break;
+    case 128:
+      if (al) hipLaunchKernelGGL((append_kernel<128, true>), grid, block, 0, s, a, bk, bv);
+      else hipLaunchKernelGGL((append_kernel<128, false>), grid, block, 0, s, a, bk, bv);
+      break;
+    default: return (int)hipErrorInvalidValue;
+  }
   return (int)hipGetLastError();
 }
 

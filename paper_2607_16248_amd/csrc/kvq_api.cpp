@@ -412,7 +412,10 @@ kvq_status kvq_append(kvq_cache* c, const void* K, const void* V, int32_t n_max,
     L_new[i] = c->L[i] + n_new[i];
     Lq_new[i] = quantized_len(L_new[i], d);
     if (n_new[i] > 0) seqs.push_back(i);
-    if ((int64_t)L_new[i] - c->Lq[i] > c->W) fused = false;
+    // a launch that both packs and fills the ring must not overwrite a slot
+    // it still reads: safe when the tokens span at most the ring, or when
+    // none of the tokens to pack sits in the ring
+    if (n_new[i] > 0 && (int64_t)L_new[i] - c->Lq[i] > c->W && c->L[i] > c->Lq[i]) fused = false;
     if (c->paged)
       pages_needed += (Lq_new[i] + d.page_tokens - 1) / d.page_tokens - (int64_t)c->pages[i].size();
   }
@@ -462,8 +465,8 @@ kvq_status kvq_append(kvq_cache* c, const void* K, const void* V, int32_t n_max,
     if (e) return hip_fail(e, "block table launch");
   }
 
-  // fused: one launch packs groups and fills ring slots (no slot is both
-  // read and written); otherwise pack first, then fill the ring.
+  // fused: one launch packs groups and fills ring slots; otherwise pack
+  // first, then fill the ring.
   const int phases = fused ? 1 : 2;
   for (int ph = 0; ph < phases; ++ph) {
     const bool quant = fused || ph == 0, copy = fused || ph == 1;
@@ -487,9 +490,10 @@ kvq_status kvq_append(kvq_cache* c, const void* K, const void* V, int32_t n_max,
         s.seq = i;
         s.L_old = c->L[i]; s.Lq_old = c->Lq[i]; s.L_new = L_new[i]; s.Lq_new = Lq_new[i];
         s.n_quant = (Lq_new[i] - c->Lq[i]) / d.key_group;
-        s.do_copy = (copy && L_new[i] > std::max(Lq_new[i], c->L[i])) ? 1 : 0;
+        const int32_t stay = L_new[i] - std::max(Lq_new[i], c->L[i]);
+        s.n_copy = copy ? (stay + kvq::kCopyTokens - 1) / kvq::kCopyTokens : 0;
         s.wg_begin = wg;
-        wg += (quant ? s.n_quant * d.num_kv_heads : 0) + (s.do_copy ? d.num_kv_heads : 0);
+        wg += ((quant ? s.n_quant : 0) + s.n_copy) * d.num_kv_heads;
       }
       a.nseq = n;
       a.total_wg = wg;

@@ -103,13 +103,16 @@ struct TableSet {
 
 // ---------------------------------------------------------------- append
 
+constexpr int kAppendThreads = 256;
+constexpr int kCopyTokens = 32;  // ring tokens one copy workgroup of a head writes
+
 struct AppendSeq {
   uint64_t head0;     // arena offset of (seq, head 0)
   int32_t seq;        // index into the input batch
   int32_t L_old, Lq_old, Lq_new, L_new;
   int32_t wg_begin;   // first workgroup of this sequence
   int32_t n_quant;    // key groups to pack per head
-  int32_t do_copy;    // 1 if this launch writes ring slots
+  int32_t n_copy;     // copy workgroups per head in this launch (ring slots written: kCopyTokens each)
 };
 
 struct AppendArgs {
