@@ -33,6 +33,7 @@ SOURCES = [
     ("append.hip", ["-ffp-contract=off"], None),
     ("decode.hip", ["-fno-honor-nans"], None),
     ("chunk_mfma.hip", ["-fno-honor-nans"], None),
+    ("prefill_mfma.hip", ["-fno-honor-nans"], None),
     ("dequant.hip", [], None),
     ("dgap.hip", [], None),
     ("noalloc.hip", [], None),
@@ -60,7 +61,7 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     workers = min(len(SOURCES), max(2, os.cpu_count() or 2))
     # the long compiles first, so that they start at once
-    order = sorted(range(len(SOURCES)), key=lambda i: SOURCES[i][0] not in ("decode_mfma.hip", "chunk_mfma.hip"))
+    order = sorted(range(len(SOURCES)), key=lambda i: SOURCES[i][0] not in ("decode_mfma.hip", "chunk_mfma.hip", "prefill_mfma.hip"))
     with cf.ThreadPoolExecutor(max_workers=workers) as ex:
         done = dict(zip(order, ex.map(lambda i: _compile(SOURCES[i][0], SOURCES[i][1], verbose, SOURCES[i][2]),
                                       order)))

@@ -666,6 +666,7 @@ int launch_r(const DecodeArgs& a, int rows, void* stream) {
 
 int launch_chunk_matrix(const DecodeArgs& a, int bk, int bv, int rows, void* stream) {
   if (a.total_wg <= 0) return 0;
+  if (a.out != nullptr) return launch_prefill(a, bk, bv, stream);
   if (bk == 1 && bv == 1) return launch_r<1, 1>(a, rows, stream);
   if (bk == 1 && bv == 2) return launch_r<1, 2>(a, rows, stream);
   if (bk == 2 && bv == 1) return launch_r<2, 1>(a, rows, stream);

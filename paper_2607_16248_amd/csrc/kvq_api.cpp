@@ -522,6 +522,7 @@ namespace {
 // groups of qpr queries, rows = qpr * (Hq / Hkv) rows per workgroup.
 struct Rows {
   int nqry = 1, qpr = 1, nrg = 1, rows = 1;
+  bool many = false;  // the many-row kernel (prefill_mfma.hip)
 };
 
 // Single-token decode: one row group of the kv head's query heads.  Chunk
@@ -584,11 +585,76 @@ Rows rows_for(const kvq_cache* c, bool matrix, int nqry, int bk, int bv) {
 
 struct SplitPlan {
   std::vector<int32_t> st, nq, ns, base;  // per sequence: split length, packed splits, all splits, first record
-  int64_t records = 0;
+  std::vector<uint8_t> direct;            // per sequence: written by the split launch, not merged
+  int64_t records = 0;   // what the launches write
+  int64_t required = 0;  // what the caller's workspace has to hold
   int nqry = 1;
 };
 
-SplitPlan plan_splits(const kvq_cache* c, int nqry = 1) {
+// Whether a class's chunk queries go to the many-row kernel, by (query, head)
+// rows per kv head and, at 4-bit keys and values, by rows times tokens:
+//   1- and 2-bit classes from 80 rows on: 96 rows of 4096 tokens (K2V2) take 24
+//   against 37 us in 32-row groups, 64 rows of 32768 tokens 44 against 40;
+//   K4V4 (which has 16-row groups of half the products per row) from 256 rows
+//   and 3 * 2^20 rows x tokens on: 512 rows of 8192 tokens 51 against 62 us, of
+//   4096 tokens 40 against 39, 256 rows of 1024 tokens 20 against 18;
+//   8-bit classes, which have 8-row groups only, from 256 rows on: 28 against
+//   37 us at 4096 tokens, 19 against 18 at 1024;
+//   value groups of 64 and 128 channels (8-row groups at any width) from 80.
+bool many_rows(const kvq_cache* c, int seq0, int nqry) {
+  if (!c->matrix[seq0] || nqry <= 1) return false;
+  const int64_t rows = (int64_t)nqry * (c->d.num_q_heads / c->d.num_kv_heads);
+  const int bk = c->bk[seq0], bv = c->bv[seq0];
+  if (bk + bv <= 4 || c->d.value_group != 32) return rows >= 80;
+  if (bk + bv > 8) return rows >= 256;
+  int64_t longest = 0;
+  for (int i = 0; i < c->d.batch; ++i)
+    if (c->bk[i] == bk && c->bv[i] == bv) longest = std::max<int64_t>(longest, c->L[i]);
+  return rows >= 256 && rows * longest >= (int64_t)3 << 20;
+}
+
+// Splits of a class on the many-row kernel: the block count per split with the
+// smallest estimated time.  One workgroup of eight waves fills a compute
+// unit, so a launch takes rounds of one workgroup per unit; each costs its
+// blocks and a fixed part, and more than one split writes and re-reads the
+// records.  The constants fit K2V2 launches of 1024 to 16384 tokens at 512
+// queries of four heads per kv head and 1 to 4 splits within 5% (8192 tokens:
+// 309 us in one split, 173 in two, 129 in three, 111 in four).
+constexpr double kBlockUs = 1.16, kSplitUs = 13.0, kRecordUs = 3.0e-4;
+int many_rows_blocks(const kvq_cache* c, const std::vector<int>& seqs, int nqry, int64_t max_records) {
+  const int gqh = c->d.num_q_heads / c->d.num_kv_heads;
+  const int nrg = (nqry + 32 / gqh - 1) / (32 / gqh), nrw = (nrg + kvq::kPrefillWaves - 1) / kvq::kPrefillWaves;
+  const int64_t bound = splits_bound(c), units = (int64_t)c->d.num_kv_heads * nrw, cus = target_workgroups(1);
+  int64_t longest = 1;
+  for (int i : seqs) longest = std::max<int64_t>(longest, (c->L[i] + 31) / 32);
+  if (c->split_tokens > 0) {
+    const int64_t bps = std::max<int64_t>(c->split_tokens / 32, (longest + bound - 1) / bound);
+    int64_t records = 0;
+    for (int i : seqs) records += ((c->L[i] + 31) / 32 + bps - 1) / bps;
+    return (int)(records <= max_records ? bps : longest);
+  }
+  double best = 0.0;
+  int64_t pick = longest;
+  for (int64_t ns = 1; ns <= std::min<int64_t>(bound, 64); ++ns) {
+    const int64_t bps = (longest + ns - 1) / ns;
+    int64_t wgs = 0, records = 0;
+    for (int i : seqs) {
+      const int64_t n = ((c->L[i] + 31) / 32 + bps - 1) / bps;
+      wgs += units * n;
+      records += n > 1 ? n : 0;
+    }
+    if (records > max_records) break;
+    const int64_t rounds = (wgs + cus - 1) / cus;
+    const double t = rounds * (bps * kBlockUs + kSplitUs) +
+                     records * (double)nqry * c->d.num_q_heads * kRecordUs;
+    if (ns == 1 || t < best) best = t, pick = bps;
+  }
+  return (int)pick;
+}
+
+// ws_bytes: the workspace at hand (the many-row kernel takes no more splits
+// than fit it; one split needs none).
+SplitPlan plan_splits(const kvq_cache* c, int nqry = 1, size_t ws_bytes = 0) {
   SplitPlan p;
   p.nqry = nqry;
   const int B = c->d.batch;
@@ -607,11 +673,35 @@ SplitPlan plan_splits(const kvq_cache* c, int nqry = 1) {
   p.nq.resize(B);
   p.ns.resize(B);
   p.base.resize(B);
+  p.direct.assign(B, 0);
   for (int i = 0; i < B; ++i) {
     p.nq[i] = (c->Lq[i] + p.st[i] - 1) / p.st[i];
     p.ns[i] = p.nq[i] + (c->L[i] > c->Lq[i] ? 1 : 0);
     p.base[i] = (int32_t)p.records;
     p.records += p.ns[i];
+  }
+  p.required = p.records;
+  bool many = false;
+  for (auto& cl : classes) many |= many_rows(c, cl.second[0], nqry);
+  if (!many) return p;
+  // re-plan the many-row classes; the records of the others come first
+  int64_t left = (int64_t)(ws_bytes / ((size_t)c->d.num_q_heads * nqry * kvq::kRecFloats * sizeof(float)));
+  p.records = 0;
+  for (int i = 0; i < B; ++i) {
+    if (many_rows(c, i, nqry)) continue;
+    p.base[i] = (int32_t)p.records;
+    p.records += p.ns[i];
+  }
+  for (auto& cl : classes) {
+    if (!many_rows(c, cl.second[0], nqry)) continue;
+    const int bps = many_rows_blocks(c, cl.second, nqry, left - p.records);
+    for (int i : cl.second) {
+      p.nq[i] = bps;
+      p.ns[i] = ((c->L[i] + 31) / 32 + bps - 1) / bps;
+      p.direct[i] = p.ns[i] <= 1;
+      p.base[i] = (int32_t)p.records;
+      p.records += p.direct[i] ? 0 : p.ns[i];
+    }
   }
   return p;
 }
@@ -627,9 +717,9 @@ struct FusedAppend {
 };
 
 kvq_status run_partials(const kvq_cache* c, const SplitPlan& p, const void* q, void* ws, size_t ws_bytes,
-                        void* stream, const FusedAppend* app = nullptr) {
+                        void* stream, const FusedAppend* app = nullptr, float* out = nullptr) {
   const kvq_cache_desc& d = c->d;
-  const size_t need = (size_t)p.records * d.num_q_heads * p.nqry * kvq::kRecFloats * sizeof(float);
+  const size_t need = (size_t)p.required * d.num_q_heads * p.nqry * kvq::kRecFloats * sizeof(float);
   if (!q) return fail(KVQ_ERR_ARG, "q must be a device pointer");
   if (need > 0 && !ws) return fail(KVQ_ERR_ARG, "workspace is NULL");
   if (ws_bytes < need) return fail(KVQ_ERR_CAPACITY, "workspace holds %zu bytes, this call needs %zu", ws_bytes, need);
@@ -650,7 +740,14 @@ kvq_status run_partials(const kvq_cache* c, const SplitPlan& p, const void* q, v
     a.hq = d.num_q_heads; a.hkv = d.num_kv_heads; a.gk = d.key_group; a.gv = d.value_group; a.W = c->W;
     a.split_tokens = p.st[cls.second[0]];
     a.qscale = qscale;
-    const Rows r = rows_for(c, c->matrix[cls.second[0]] != 0, p.nqry, cls.first.first, cls.first.second);
+    Rows r = rows_for(c, c->matrix[cls.second[0]] != 0, p.nqry, cls.first.first, cls.first.second);
+    if (many_rows(c, cls.second[0], p.nqry)) {
+      r.many = true;
+      r.rows = 32;
+      r.qpr = 32 / (d.num_q_heads / d.num_kv_heads);
+      r.nrg = (p.nqry + r.qpr - 1) / r.qpr;
+      a.out = out;
+    }
     a.nqry = r.nqry; a.qpr = r.qpr; a.nrg = r.nrg; a.gqh = d.num_q_heads / d.num_kv_heads;
     // rows past qpr whole queries (a chunk kernel group of five heads) are
     // spare: row_x = kvq::kSpareRow marks them (a repeat of the last query)
@@ -672,7 +769,8 @@ kvq_status run_partials(const kvq_cache* c, const SplitPlan& p, const void* q, v
       s.L_old = app ? (*app->L_old)[i] : c->L[i];
       s.nq = p.nq[i]; s.nsplit = p.ns[i]; s.ws_base = p.base[i];
       s.wg_begin = wg;
-      wg += p.ns[i] * d.num_kv_heads * r.nrg;
+      const int row_wgs = r.many ? (r.nrg + kvq::kPrefillWaves - 1) / kvq::kPrefillWaves : r.nrg;
+      wg += p.ns[i] * d.num_kv_heads * row_wgs;
     }
     a.nseq = n;
     a.total_wg = wg;
@@ -695,6 +793,7 @@ kvq_status run_merge(const kvq_cache* c, const SplitPlan& p, const void* ws, flo
     m.hq = d.num_q_heads * p.nqry;  // out [batch][nqry][Hq] = [batch][nqry * Hq]
     int n = 0;
     for (int i = b; i < std::min(d.batch, b + kvq::kMaxSeqPerLaunch); ++i) {
+      if (p.direct[i]) continue;
       m.seq[n].seq = i; m.seq[n].nsplit = p.ns[i]; m.seq[n].ws_base = p.base[i];
       ++n;
     }
@@ -817,8 +916,8 @@ kvq_status kvq_chunk_attention(const kvq_cache* c, const void* q, int32_t n_q, f
   for (int i = 0; i < c->d.batch; ++i)
     if (c->L[i] < n_q)
       return fail(KVQ_ERR_ARG, "sequence %d holds %d tokens, fewer than the %d chunk queries", i, c->L[i], n_q);
-  const SplitPlan p = plan_splits(c, n_q);
-  kvq_status st = run_partials(c, p, q, ws, ws_bytes, stream);
+  const SplitPlan p = plan_splits(c, n_q, ws_bytes);
+  kvq_status st = run_partials(c, p, q, ws, ws_bytes, stream, nullptr, out);
   if (st != KVQ_OK) return st;
   st = run_merge(c, p, ws, out, stream);
   if (st != KVQ_OK) return st;

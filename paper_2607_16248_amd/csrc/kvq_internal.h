@@ -173,6 +173,10 @@ struct DecodeArgs {
   // (host-computed, so the kernels divide nothing)
   int32_t row_off[32], row_x[32];
   PageMap pm;
+  // many-row chunk launches (launch_prefill): per sequence, nq is the 32-token
+  // blocks per split and nsplit the splits over packed and tail tokens
+  // together; a sequence of one split is written to out
+  float* out;         // fp32 [batch][nqry][Hq][128]
 };
 
 struct MergeSeq {
@@ -259,6 +263,11 @@ bool matrix_decode_supported(int bk, int bv, int gq, int gk, int gv, uint64_t he
 int matrix_decode_occupancy(int bk, int bv, int gk, int gq);
 // Chunk queries over row groups of 16 or 32 rows (chunk_mfma.hip).
 int launch_chunk_matrix(const DecodeArgs& a, int bk, int bv, int rows, void* stream);
+// Chunk queries of many rows: kPrefillWaves row groups of 32 rows per
+// workgroup (prefill_mfma.hip; launch_chunk_matrix hands it the launches that
+// carry out).
+constexpr int kPrefillWaves = 8;
+int launch_prefill(const DecodeArgs& a, int bk, int bv, void* stream);
 // The matrix-core decode kernels of one bit class (decode_mfma.hip, one
 // object per class); launch_decode_matrix (matrix_dispatch.cpp) picks one.
 template <int BK, int BV>
