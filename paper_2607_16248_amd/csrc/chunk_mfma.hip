@@ -37,6 +37,7 @@
 #include "kvq_internal.h"
 #include "kvq_layout.h"
 #include "mfma_common.h"
+#include "tail_mfma.h"
 
 namespace kvq {
 namespace {
@@ -51,9 +52,7 @@ constexpr int kPR = 36;             // floats per weight row (32 + 4)
 constexpr int kZG = 16;             // key groups per zero-point table
 
 // LDS areas (bytes) of a workgroup of NU row halves (16 * NU rows).  The
-// first holds the cross-wave reduction after the loop, or the staged query
-// rows of the fp16-tail splits (per wave).
-constexpr int kTailQ = kHeadDim * 8;  // floats of one wave's staged query rows (8 rows)
+// first holds the cross-wave reduction after the loop.
 template <int NU>
 struct ChunkSmem {
   static constexpr int R = kRows * NU;
@@ -68,8 +67,6 @@ struct ChunkSmem {
   static constexpr int kOffLM = kOffCS + R * 4;
   static constexpr int kOffVT = kOffLM + R * 4;
   static constexpr int kBytes = kOffVT + ValueTable2::kWords * 4;
-  static_assert(kWaves * kTailQ * 4 <= kBytesQA, "the tail splits' query rows fit the first area");
-  static_assert(32 * 8 <= R * kPR, "a tail half's weights fit its wave's weight area");
 };
 
 // Everything one 32-token block reads from memory.
@@ -96,7 +93,6 @@ chunk_mfma_kernel(DecodeArgs a) {
   constexpr int R = SM::R;
   constexpr bool kPairW = BV == 1;  // 1-bit value operands carry pair weights 2^t
   __shared__ __attribute__((aligned(16))) uint8_t smem[SM::kBytes];
-  uint32_t* const qa_all = reinterpret_cast<uint32_t*>(smem + SM::kOffQA);
   float* const pl_all = reinterpret_cast<float*>(smem + SM::kOffPL);
   uint32_t* const vm_all = reinterpret_cast<uint32_t*>(smem + SM::kOffVM);
   float* const dz_all = reinterpret_cast<float*>(smem + SM::kOffDZ);
@@ -114,20 +110,15 @@ chunk_mfma_kernel(DecodeArgs a) {
   uint32_t vbound = __builtin_amdgcn_raw_buffer_load_b32(head_rsrc(blk + a.vb, 4), 0, 0, 0);
   asm volatile("" ::: "memory");
 
-  if (wk.sp >= S.nq) {  // fp16 tail tokens: the vector path, in parts of 8 rows
-    uint32_t* qa = qa_all + wv * kTailQ;
-    for (int half = 0; half < 2 * NU; ++half) {
-      float qs0[8], qs1[8];
-      load_q_scaled<8, true>(a, S, wk.h, wk.rg, lane, qs0, qs1, 8 * half);
-      State<8> st;
-      init_state<8>(st);
-      tail_split<8, true>(a, S, wk.h, wk.rg, blk, qs0, qs1, reinterpret_cast<float*>(qa), pl_all + wv * R * kPR, st,
-                          lane, wv, 8 * half);
-      __syncthreads();  // every wave is done with its area before the reduction overlays it
-      stage_state<8>(st, red, lane, wv);
+  if (wk.sp >= S.nq) {  // fp16 tail tokens; the reduction takes 8 rows at a time
+    TailState<NU> st;
+    tail_split<NU, R, true>(a, S, wk.h, wk.rg, blk, st, lane, wv);
+#pragma unroll
+    for (int part = 0; part < 2 * NU; ++part) {
+      stage_tail<8, NU>(st, part >> 1, 8 * part, red, lane, wv);
       __syncthreads();
-      write_record<8, true>(a, S, wk.h, wk.rg, wk.sp, red, 8 * half);
-      __syncthreads();  // the reduction is read before the next part's query overlays it
+      write_record<8, true>(a, S, wk.h, wk.rg, wk.sp, red, 8 * part);
+      __syncthreads();  // the reduction is read before the next part overlays it
     }
     return;
   }

@@ -19,6 +19,7 @@
 
 #include "decode_common.h"
 #include "kvq_internal.h"
+#include "tail_mfma.h"
 
 namespace kvq {
 namespace {
@@ -158,7 +159,12 @@ __global__ __launch_bounds__(256) void decode_split_kernel(DecodeArgs a) {
     for (int j = t0 / a.gk + wv; j < t1 / a.gk; j += kWaves)
       packed_group<BK, BV, GQ>(a, S, wk.h, j, qs0, qs1, qp, pl, st, lim, glim, lane);
   } else {
-    tail_split<GQ, true>(a, S, wk.h, wk.rg, blk, qs0, qs1, qp, pl, st, lane, wv);
+    TailState<1> ts;
+    tail_split<1, GQ, true>(a, S, wk.h, wk.rg, blk, ts, lane, wv);
+    stage_tail<GQ, 1>(ts, 0, 0, red, lane, wv);
+    __syncthreads();
+    write_record<GQ, true>(a, S, wk.h, wk.rg, wk.sp, red);
+    return;
   }
   stage_state<GQ>(st, red, lane, wv);
   __syncthreads();

@@ -1,6 +1,6 @@
 // Pieces shared by the decode kernels: wave reductions over DPP, the
-// online-softmax state of the vector path, the fp16-tail pass, and the
-// combination of per-wave partial results into one split record.
+// online-softmax state of the vector path, and the combination of per-wave
+// partial results into one split record.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -93,59 +93,6 @@ __device__ __forceinline__ void softmax_pass(State<GQ>& st, float (&sig)[GQ], in
     st.m[g] = mnew;
     if (!half) p_lds[tl * GQ + g] = p;
   }
-}
-
-// fp16 tail tokens [Lq, L), read from the ring; pass `pass` covers 32 tokens.
-template <int GQ, bool CHUNK>
-__device__ __forceinline__ void tail_pass(const DecodeArgs& a, const DecodeSeq& S, const uint8_t* blk,
-                                          int pass, const float* qp, float* p_lds, State<GQ>& st,
-                                          const int (&lim)[GQ], int lane) {
-  constexpr int QS = QStride<GQ>::value;
-  const int ntail = S.L - S.Lq;
-  const int tl = lane >> 1, half = lane & 1;
-  const int idx = pass * 32 + tl;
-  float sig[GQ];
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) sig[g] = 0.f;
-  if (idx < ntail) {
-    const int slot = (S.Lq + idx) % a.W;
-    const uint4* kr = reinterpret_cast<const uint4*>(blk + a.tk + ((size_t)slot * kHeadDim + half * 64) * 2);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint4 v = kr[i];
-      const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = h2f((w4[e >> 1] >> ((e & 1) * 16)) & 0xFFFF);
-        const float* qv = qp + (half * 64 + i * 8 + e) * QS;
-#pragma unroll
-        for (int g = 0; g < GQ; ++g) sig[g] = fmaf(qv[g], x, sig[g]);
-      }
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    sig[g] += dpp_mov<kQuadXor1>(0.f, sig[g]);
-    if (idx >= ntail || (CHUNK && S.Lq + idx >= lim[g])) sig[g] = -__builtin_inff();
-  }
-  softmax_pass<GQ, CHUNK>(st, sig, half, tl, p_lds);
-  wave_lds_sync();
-  const int tq = lane >> 4, cc = lane & 15;
-  for (int tt = tq; tt < 32; tt += 4) {
-    const int i2 = pass * 32 + tt;
-    if (i2 >= ntail) break;
-    const int slot = (S.Lq + i2) % a.W;
-    const uint4 v = *reinterpret_cast<const uint4*>(blk + a.tv + ((size_t)slot * kHeadDim + cc * 8) * 2);
-    const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-    const float* pp = p_lds + tt * GQ;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float x = h2f((w4[k >> 1] >> ((k & 1) * 16)) & 0xFFFF);
-#pragma unroll
-      for (int g = 0; g < GQ; ++g) st.acc[g][k] = fmaf(pp[g], x, st.acc[g][k]);
-    }
-  }
-  wave_lds_sync();
 }
 
 // Locate this workgroup's (sequence, kv head, row group, split).
@@ -302,42 +249,6 @@ __device__ __forceinline__ void write_record(const DecodeArgs& a, const DecodeSe
     rec[4 + c] = val;
     if (c == 0) { rec[0] = M; rec[1] = lsum; }
   }
-}
-
-// The fp16 tail split: every wave takes passes of 32 tokens.
-template <int GQ, bool CHUNK>
-__device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq& S, int h, int rg,
-                                           const uint8_t* blk, const float (&qs0)[GQ], const float (&qs1)[GQ],
-                                           float* qp, float* pl, State<GQ>& st, int lane, int wv, int g0 = 0) {
-  constexpr int QS = QStride<GQ>::value;
-  // Fused append: this workgroup alone reads the ring of (sequence, head h)
-  // in this launch; it first stores the tokens appended by the call, which
-  // all stay fp16 (the host takes this path only when no key group fills).
-  if (a.K_new != nullptr && S.L_old < S.L) {
-    uint32_t* rk = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(blk) + a.tk);
-    uint32_t* rv = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(blk) + a.tv);
-    const uint32_t* ik = reinterpret_cast<const uint32_t*>(a.K_new);
-    const uint32_t* iv = reinterpret_cast<const uint32_t*>(a.V_new);
-    constexpr int kRow = kHeadDim / 2;  // dwords per token row
-    for (int idx = threadIdx.x; idx < (S.L - S.L_old) * kRow; idx += blockDim.x) {
-      const int t = idx / kRow, c = idx % kRow;
-      const size_t src = (((size_t)S.seq * a.n_max + t) * a.hkv + h) * kRow + c;
-      const size_t dst = (size_t)((S.L_old + t) % a.W) * kRow + c;
-      rk[dst] = ik[src];
-      rv[dst] = iv[src];
-    }
-    __syncthreads();  // the stores are visible to the whole workgroup
-  }
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    qp[(2 * lane) * QS + g] = qs0[g];
-    qp[(2 * lane + 1) * QS + g] = qs1[g];
-  }
-  wave_lds_sync();
-  int lim[GQ];
-  row_limits<GQ>(a, S, h, rg, lim, g0);
-  for (int pass = wv; pass * 32 < S.L - S.Lq; pass += kWaves)
-    tail_pass<GQ, CHUNK>(a, S, blk, pass, qp, pl, st, lim, lane);
 }
 
 template <int GQ>

@@ -60,6 +60,7 @@
 #include "kvq_internal.h"
 #include "kvq_layout.h"
 #include "mfma_common.h"
+#include "tail_mfma.h"
 
 namespace kvq {
 namespace {
@@ -210,7 +211,7 @@ decode_mfma_kernel(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t qq_s[NH * kQRow];
   __shared__ uint32_t qt_s[NH][64];
   __shared__ float cs_s[NH];
-  __shared__ __attribute__((aligned(16))) float p_lds[kWaves][kPRow * NH];  // weights to the value layout; fp16 tail split
+  __shared__ __attribute__((aligned(16))) float p_lds[kWaves][kPRow * NH];  // weights to the value layout
   __shared__ Reduce<GQ> red;
   // value operand halves of each byte of packed 2-bit codes (its 2-bit fields)
   constexpr int kTabWords = BV == 2 ? ValueTable2::kWords : 4;
@@ -229,16 +230,10 @@ decode_mfma_kernel(DecodeArgs a) {
   uint32_t vbound = __builtin_amdgcn_raw_buffer_load_b32(head_rsrc(blk + a.vb, 4), 0, 0, 0);
   asm volatile("" ::: "memory");
 
-  if (wk.sp >= S.nq) {  // fp16 tail tokens: vector path
-    float qs0[GQ], qs1[GQ];
-    load_q_scaled<GQ, CAUSAL>(a, S, wk.h, wk.rg, lane, qs0, qs1);
-    State<GQ> st;
-    init_state<GQ>(st);
-    static_assert(kHeadDim * QStride<GQ>::value <= (2 * NH + kDzRows) * kQRow, "tail query fits the Q' area");
-    static_assert(32 * GQ <= kPRow * NH, "tail weights fit the weight area");
-    tail_split<GQ, CAUSAL>(a, S, wk.h, wk.rg, blk, qs0, qs1, reinterpret_cast<float*>(q_lds[wv]), p_lds[wv], st,
-                           lane, wv);
-    stage_state<GQ>(st, red, lane, wv);
+  if (wk.sp >= S.nq) {  // fp16 tail tokens
+    TailState<1> st;
+    tail_split<1, GQ, CAUSAL>(a, S, wk.h, wk.rg, blk, st, lane, wv);
+    stage_tail<GQ, 1>(st, 0, 0, red, lane, wv);
     __syncthreads();
     write_record<GQ, CAUSAL>(a, S, wk.h, wk.rg, wk.sp, red);
     return;
