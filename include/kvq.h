@@ -252,8 +252,7 @@ size_t kvq_export_bytes(const kvq_cache* cache, int32_t seq, int32_t kv_head);
  * `bytes` >= kvq_export_bytes(...): the persistent low-bit cache the paper
  * keeps unchanged across decode steps (Methodology, "DGAP Overview", online
  * restoration framework), in the byte order above, for checking and for
- * saving a cache.  Device-to-device copies and a reorder kernel on
- * `stream`.  Errors: KVQ_ERR_ARG (seq or kv_head out of range, null dst),
+ * saving a cache.  One kernel on `stream`.  Errors: KVQ_ERR_ARG (seq or kv_head out of range, null dst),
  * KVQ_ERR_CAPACITY (bytes too small), KVQ_ERR_HIP. */
 kvq_status kvq_export(const kvq_cache* cache, int32_t seq, int32_t kv_head, void* dst,
                       size_t bytes, void* stream);

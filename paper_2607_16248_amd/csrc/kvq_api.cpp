@@ -966,92 +966,24 @@ kvq_status kvq_export(const kvq_cache* c, int32_t seq, int32_t h, void* dst, siz
   if (need == 0) return ok();
   if (!dst) return fail(KVQ_ERR_ARG, "destination is NULL");
   const HeadLayout& lay = c->lay[seq];
-  const uint8_t* blk = c->arena + c->head0[seq] + (uint64_t)h * lay.stride;
-  uint8_t* o = static_cast<uint8_t*>(dst);
-  const size_t Lq = c->Lq[seq], L = c->L[seq], D = kvq::kHeadDim;
-  const size_t part[4][2] = {{lay.kc, Lq * 16 * c->bk[seq]},
-                             {lay.km, Lq / c->d.key_group * 2 * D * 2},
-                             {lay.vc, Lq * 16 * c->bv[seq]},
-                             {lay.vm, Lq * (D / c->d.value_group) * 4}};
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (c->paged) {
-    // page by page into the same canonical image: the page's tokens
-    // [t0, t0 + n) of every part, codes and value meta re-ordered by the
-    // export kernel in the matrix layout
-    uint8_t* okc = o;
-    uint8_t* okm = okc + part[0][1];
-    uint8_t* ovc = okm + part[1][1];
-    uint8_t* ovm = ovc + part[2][1];
-    const size_t P = c->d.page_tokens, gk = c->d.key_group, ng = D / c->d.value_group;
-    const int bk = c->bk[seq], bv = c->bv[seq];
-    for (size_t lp = 0; lp * P < Lq; ++lp) {
-      const size_t t0 = lp * P, n = std::min(Lq - t0, P);
-      const uint8_t* seg =
-          c->arena + c->pm.pool0 + (uint64_t)c->pages[seq][lp] * c->pm.page_bytes + (uint64_t)h * c->pm.page_head_bytes;
-      const hipError_t e = hipMemcpyAsync(okm + t0 / gk * 2 * D * 2, seg + lay.km, n / gk * 2 * D * 2,
-                                          hipMemcpyDeviceToDevice, s);
-      if (e != hipSuccess) return hip_fail(e, "export copy");
-      if (c->matrix[seq]) {
-        kvq::ExportArgs x{};
-        x.blk = seg;
-        x.kc_out = okc + t0 * 16 * bk;
-        x.vc_out = ovc + t0 * 16 * bv;
-        x.vm_out = ovm + t0 * ng * 4;
-        x.kc = (uint32_t)lay.kc; x.vc = (uint32_t)lay.vc; x.vm = (uint32_t)lay.vm;
-        x.bk = bk; x.bv = bv; x.gv = c->d.value_group; x.nblocks = (int32_t)(n / 32);
-        const int ek = kvq::launch_export(x, stream);
-        if (ek) return hip_fail(ek, "export launch");
-      } else {
-        const size_t src[3][3] = {{lay.kc, t0 * 16 * bk, n * 16 * bk},
-                                  {lay.vc, t0 * 16 * bv, n * 16 * bv},
-                                  {lay.vm, t0 * ng * 4, n * ng * 4}};
-        uint8_t* dst[3] = {okc, ovc, ovm};
-        for (int k = 0; k < 3; ++k) {
-          const hipError_t e2 = hipMemcpyAsync(dst[k] + src[k][1], seg + src[k][0], src[k][2],
-                                               hipMemcpyDeviceToDevice, s);
-          if (e2 != hipSuccess) return hip_fail(e2, "export copy");
-        }
-      }
-    }
-    o = ovm + part[3][1];
-  } else if (c->matrix[seq]) {
-    // key meta is stored canonically; codes and value meta are re-ordered by a kernel
-    if (part[1][1]) {
-      const hipError_t e = hipMemcpyAsync(o + part[0][1], blk + part[1][0], part[1][1], hipMemcpyDeviceToDevice, s);
-      if (e != hipSuccess) return hip_fail(e, "export copy");
-    }
-    kvq::ExportArgs x{};
-    x.blk = blk;
-    x.kc_out = o;
-    x.vc_out = o + part[0][1] + part[1][1];
-    x.vm_out = x.vc_out + part[2][1];
-    x.kc = (uint32_t)lay.kc; x.vc = (uint32_t)lay.vc; x.vm = (uint32_t)lay.vm;
-    x.bk = c->bk[seq]; x.bv = c->bv[seq]; x.gv = c->d.value_group; x.nblocks = (int32_t)(Lq / 32);
-    const int e = kvq::launch_export(x, stream);
-    if (e) return hip_fail(e, "export launch");
-    o += part[0][1] + part[1][1] + part[2][1] + part[3][1];
-  } else {
-    for (auto& p : part) {
-      if (p[1] == 0) continue;
-      const hipError_t e = hipMemcpyAsync(o, blk + p[0], p[1], hipMemcpyDeviceToDevice, s);
-      if (e != hipSuccess) return hip_fail(e, "export copy");
-      o += p[1];
-    }
-  }
-  const size_t W = c->W, n = L - Lq, first = Lq % W;
-  for (uint64_t ring : {lay.tk, lay.tv}) {
-    const size_t a1 = std::min(n, W - first), a2 = n - a1;
-    if (a1) {
-      const hipError_t e = hipMemcpyAsync(o, blk + ring + first * D * 2, a1 * D * 2, hipMemcpyDeviceToDevice, s);
-      if (e != hipSuccess) return hip_fail(e, "export copy");
-      o += a1 * D * 2;
-    }
-    if (a2) {
-      const hipError_t e = hipMemcpyAsync(o, blk + ring, a2 * D * 2, hipMemcpyDeviceToDevice, s);
-      if (e != hipSuccess) return hip_fail(e, "export copy");
-      o += a2 * D * 2;
-    }
-  }
+  const size_t Lq = c->Lq[seq], tail = c->L[seq] - c->Lq[seq], D = kvq::kHeadDim;
+  kvq::ExportArgs x{};
+  x.arena = c->arena;
+  x.head0 = c->head0[seq];
+  x.head_stride = lay.stride;
+  x.kc_out = static_cast<uint8_t*>(dst);
+  x.km_out = x.kc_out + Lq * 16 * c->bk[seq];
+  x.vc_out = x.km_out + Lq / c->d.key_group * 2 * D * 2;
+  x.vm_out = x.vc_out + Lq * 16 * c->bv[seq];
+  x.tk_out = x.vm_out + Lq * (D / c->d.value_group) * 4;
+  x.tv_out = x.tk_out + tail * D * 2;
+  x.kc = (uint32_t)lay.kc; x.km = (uint32_t)lay.km; x.vc = (uint32_t)lay.vc;
+  x.vm = (uint32_t)lay.vm; x.tk = (uint32_t)lay.tk; x.tv = (uint32_t)lay.tv;
+  x.bk = c->bk[seq]; x.bv = c->bv[seq]; x.gk = c->d.key_group; x.gv = c->d.value_group; x.W = c->W;
+  x.Lq = (int32_t)Lq; x.ntail = (int32_t)tail; x.matrix = c->matrix[seq]; x.seq = seq; x.h = h;
+  x.pm = c->pm;
+  const int e = kvq::launch_export(x, stream);
+  if (e) return hip_fail(e, "export launch");
   return ok();
 }
 

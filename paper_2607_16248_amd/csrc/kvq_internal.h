@@ -231,15 +231,22 @@ struct DequantArgs {
 
 // ---------------------------------------------------------------- export
 
-// Matrix-layout codes and value meta of one (seq, head) rewritten in the
-// canonical order: 32-token blocks [0, Lq / 32).
+// The canonical image of one (seq, head): packed codes and meta of 32-token
+// blocks [0, Lq / 32) (re-ordered from the matrix layout, or copied), then the
+// fp16 tail's rows in token order.
 struct ExportArgs {
-  const uint8_t* blk;   // (seq, head) block
-  uint8_t* kc_out;      // canonical key codes [Lq][16*bk]
-  uint8_t* vc_out;      // canonical value codes [Lq][16*bv]
-  uint8_t* vm_out;      // canonical value meta [Lq][128/gv][2] fp16
-  uint32_t kc, vc, vm;
-  int32_t bk, bv, gv, nblocks;
+  const uint8_t* arena;
+  uint64_t head0;       // (seq, head 0) block (paged: the sequence's ring region)
+  uint64_t head_stride;
+  uint8_t* kc_out;      // key codes [Lq][16*bk]
+  uint8_t* km_out;      // key meta [Lq/gk][2][128] fp16
+  uint8_t* vc_out;      // value codes [Lq][16*bv]
+  uint8_t* vm_out;      // value meta [Lq][128/gv][2] fp16
+  uint8_t* tk_out;      // key tail [ntail][128] fp16
+  uint8_t* tv_out;      // value tail [ntail][128] fp16
+  uint32_t kc, km, vc, vm, tk, tv;
+  int32_t bk, bv, gk, gv, W, Lq, ntail, matrix, seq, h;
+  PageMap pm;
 };
 
 // Launchers (defined next to their kernels).  Return a hipError_t as int.
