@@ -25,13 +25,14 @@ COMMON = [f"--offload-arch={ARCH}", "-O3", "-fPIC", "-std=c++17",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
-# The matrix-core decode source is compiled once per bit class (its kernels
-# are many template instantiations), so that the classes build in parallel.
+# The matrix-core decode sources are compiled once per bit class or key width
+# (their kernels are many template instantiations), so that they build in
+# parallel.
 MATRIX_CLASSES = [(1, 1), (1, 2), (2, 1), (2, 2), (4, 4), (4, 8), (8, 4), (8, 8)]
 
 SOURCES = [
     ("append.hip", ["-ffp-contract=off"], None),
-    ("decode.hip", ["-fno-honor-nans"], None),
+    ("merge.hip", ["-fno-honor-nans"], None),
     ("chunk_mfma.hip", ["-fno-honor-nans"], None),
     ("prefill_mfma.hip", ["-fno-honor-nans"], None),
     ("dequant.hip", [], None),
@@ -40,7 +41,8 @@ SOURCES = [
     ("matrix_dispatch.cpp", [], None),
     ("kvq_api.cpp", [], None),
 ] + [("decode_mfma.hip", ["-fno-honor-nans", f"-DKVQ_BK={bk}", f"-DKVQ_BV={bv}"], f"decode_mfma_k{bk}v{bv}.o")
-     for bk, bv in MATRIX_CLASSES]
+     for bk, bv in MATRIX_CLASSES] + [
+    ("decode_exact.hip", ["-fno-honor-nans", f"-DKVQ_BK={bk}"], f"decode_exact_k{bk}.o") for bk in (1, 2, 4, 8)]
 
 
 def _compile(src, extra, verbose, obj_name=None):
@@ -61,7 +63,7 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     workers = min(len(SOURCES), max(2, os.cpu_count() or 2))
     # the long compiles first, so that they start at once
-    order = sorted(range(len(SOURCES)), key=lambda i: SOURCES[i][0] not in ("decode_mfma.hip", "chunk_mfma.hip", "prefill_mfma.hip"))
+    order = sorted(range(len(SOURCES)), key=lambda i: SOURCES[i][0] not in ("decode_mfma.hip", "decode_exact.hip", "chunk_mfma.hip", "prefill_mfma.hip"))
     with cf.ThreadPoolExecutor(max_workers=workers) as ex:
         done = dict(zip(order, ex.map(lambda i: _compile(SOURCES[i][0], SOURCES[i][1], verbose, SOURCES[i][2]),
                                       order)))

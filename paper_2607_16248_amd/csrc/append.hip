@@ -24,7 +24,6 @@
 //     operand.  (min, -max) of a token travel as one packed pair; a butterfly
 //     over the 16 lanes leaves lane t with token t's pair, so a wave computes
 //     all its scales at once and row broadcasts hand them back.
-//   - the canonical layout keeps 8 channels per lane for both.
 // Codes need no division: see threshold() and quantize().  Measured, against one thread per channel with
 // fp64 quotients and bit-by-bit packing: 16384 tokens at K2V2 43 us (164 in
 // two launches), 131072 tokens at K1V1 175 us or 3.4 TB/s (1034), the key
@@ -235,28 +234,7 @@ struct Rows {
   }
 };
 
-// Eight codes of consecutive channels as B bytes of a canonical row (4 and 8
-// bits; one and two bits: even channels' codes at 2*B*i of the low half of
-// acc, odd ones' of the high half).
-template <int B>
-__device__ __forceinline__ void store8(const uint32_t (&c)[8], uint8_t* rowp, int cc) {
-  uint32_t lo = 0u, hi = 0u;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    if (B < 8 || e < 4) lo |= c[e] << (B * e);
-    else hi |= c[e] << (8 * (e - 4));
-  }
-  if constexpr (B == 4) reinterpret_cast<uint32_t*>(rowp)[cc] = lo;
-  else reinterpret_cast<uint2*>(rowp)[cc] = make_uint2(lo, hi);
-}
-template <int B>
-__device__ __forceinline__ void store_row_bits(uint32_t acc, uint8_t* rowp, int cc) {
-  const uint32_t v = (acc & 0xFFFFu) | (acc >> (16 - B));
-  if constexpr (B == 1) rowp[cc] = (uint8_t)v;
-  else reinterpret_cast<uint16_t*>(rowp)[cc] = (uint16_t)v;
-}
-
-// The lane's part of its key row dwords (matrix layout, kvq_layout.h: key_bit)
+// The lane's part of its key row dwords (kvq_layout.h: key_bit)
 // into the row at o: operand block kb, lane group g4.
 template <int B>
 __device__ __forceinline__ void store_key_words(const uint32_t (&w)[2], int kb, int g4, uint32_t* o) {
@@ -277,10 +255,10 @@ __device__ __forceinline__ void store_key_words(const uint32_t (&w)[2], int kb, 
 }
 
 // Keys of one group, second half: codes of the lane's 8 channels of the
-// tokens t = 16*i + 4*wv + row, written in either layout.  par: per channel,
+// tokens t = 16*i + 4*wv + row.  par: per channel,
 // the thresholds [k][128] (fp16) at one and two bits, (scale, zero) else.
 template <int B, int GK>
-__device__ __forceinline__ void key_codes(const u4_t (&x)[GK / 16], const uint32_t* par, bool matrix, uint8_t* dst,
+__device__ __forceinline__ void key_codes(const u4_t (&x)[GK / 16], const uint32_t* par, uint8_t* dst,
                                           int lane, int wv) {
   const int cc = lane & 15, row = lane >> 4, kb = cc >> 2, g4 = cc & 3;
   if constexpr (B <= 2) {
@@ -297,17 +275,10 @@ __device__ __forceinline__ void key_codes(const u4_t (&x)[GK / 16], const uint32
         Thresholds<B> T;
 #pragma unroll
         for (int k = 0; k < NT; ++k) T.t[k] = tk[k][m];
-        // matrix: pair m at bits B*m and 16 + B*m; rows: even channels at
-        // 2*B*m of the low half, odd ones of the high half
-        if (matrix) add_codes<B>(x[i][m], T, B * m, acc);
-        else add_codes<B>(x[i][m], T, 2 * B * m, acc);
+        add_codes<B>(x[i][m], T, B * m, acc);  // pair m at bits B*m and 16 + B*m
       }
-      if (matrix) {
-        const uint32_t w[2] = {acc, 0u};
-        store_key_words<B>(w, kb, g4, reinterpret_cast<uint32_t*>(rowp));
-      } else {
-        store_row_bits<B>(acc, rowp, cc);
-      }
+      const uint32_t w[2] = {acc, 0u};
+      store_key_words<B>(w, kb, g4, reinterpret_cast<uint32_t*>(rowp));
     }
   } else {
     Grid g[8];
@@ -320,17 +291,13 @@ __device__ __forceinline__ void key_codes(const u4_t (&x)[GK / 16], const uint32
 #pragma unroll
       for (int e = 0; e < 8; ++e) c[e] = quantize<B>(e & 1 ? hi_f(x[i][e >> 1]) : lo_f(x[i][e >> 1]), g[e]);
       uint8_t* rowp = dst + (size_t)(16 * i + 4 * wv + row) * 16 * B;
-      if (matrix) {
-        uint32_t w[2] = {0u, 0u};
+      uint32_t w[2] = {0u, 0u};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if constexpr (B == 8) w[e >> 2] |= c[e] << (8 * (e & 3));
-          else w[0] |= c[e] << (B * (e >> 1) + 16 * (e & 1));
-        }
-        store_key_words<B>(w, kb, g4, reinterpret_cast<uint32_t*>(rowp));
-      } else {
-        store8<B>(c, rowp, cc);
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (B == 8) w[e >> 2] |= c[e] << (8 * (e & 3));
+        else w[0] |= c[e] << (B * (e >> 1) + 16 * (e & 1));
       }
+      store_key_words<B>(w, kb, g4, reinterpret_cast<uint32_t*>(rowp));
     }
   }
 }
@@ -352,11 +319,12 @@ __device__ __forceinline__ void for_tokens(F f) {
   f(std::integral_constant<int, 6>{}); f(std::integral_constant<int, 7>{});
 }
 
-// Values of one 32-token block, matrix layout: wave wv = K-group, lane =
-// channels 2*lane, 2*lane + 1, x[t] = token value_token(wv, t).  Returns the
+// Values of one 32-token block: wave wv = K-group, lane =
+// channels 2*lane, 2*lane + 1, x[t] = token value_token(wv, t).  FINE: groups
+// of 8 or 16 channels.  Returns the
 // wave's largest scale (fp16 bits).
-template <int B>
-__device__ __forceinline__ uint32_t value_block_matrix(uint8_t* arena, uint32_t (&x)[8], int gv, uint8_t* vcb,
+template <int B, bool FINE>
+__device__ __forceinline__ uint32_t value_block(uint8_t* arena, uint32_t (&x)[8], int gv, uint8_t* vcb,
                                                        uint8_t* vmb, int lane, int wv) {
   uint32_t m[8], nan = 0u;
 #pragma unroll
@@ -372,43 +340,78 @@ __device__ __forceinline__ uint32_t value_block_matrix(uint8_t* arena, uint32_t 
         x[t] = finite_or_zero(x[t]);
       }
   }
-  // butterfly over the 16 lanes of a row: lane ends with token (lane & 7)
+  // butterfly over four lanes: o[j] = token 4j + (lane & 3) of their 8 channels
   const bool b0 = lane & 1, b1 = lane & 2;
   uint32_t n[4], o[2];
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     n[j] = pk_min(b0 ? m[2 * j + 1] : m[2 * j], dpp<dec::kQuadXor1>(b0 ? m[2 * j] : m[2 * j + 1]));
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < 2; ++j)
     o[j] = pk_min(b1 ? n[2 * j + 1] : n[2 * j], dpp<dec::kQuadXor2>(b1 ? n[2 * j] : n[2 * j + 1]));
-    o[j] = pk_min(o[j], dpp<kRowRor4>(o[j]));
-    o[j] = pk_min(o[j], dpp<kRowRor8>(o[j]));
+  // the rest of the group's lanes; a lane then takes token (lane & 7), groups
+  // of 8 channels both of its tokens
+  const int lpg = gv / 2, ng = kHeadDim / gv;  // lanes per group
+  uint32_t sz, sz2 = 0u;
+  uint16_t* meta = reinterpret_cast<uint16_t*>(vmb);  // scales [g][pos], then zeros (value_meta_s / value_meta_z)
+  auto put_meta = [&](int g, int t, uint32_t v) {
+    meta[g * 32 + 8 * wv + t] = (uint16_t)v;
+    meta[(ng + g) * 32 + 8 * wv + t] = (uint16_t)(v >> 16);
+  };
+  if constexpr (!FINE) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      o[j] = pk_min(o[j], dpp<kRowRor4>(o[j]));
+      o[j] = pk_min(o[j], dpp<kRowRor8>(o[j]));
+    }
+    uint32_t v = (lane & 4) ? o[1] : o[0];
+    if (gv >= 64) v = join16(v, pk_min);
+    if (gv >= 128) v = join32(v, pk_min);
+    sz = scale_zero<B>(arena, lo_f(v), -hi_f(v));
+    if ((lane & 15) < 8 && (lane & (lpg - 1)) < 16) put_meta(lane / lpg, lane & 7, sz);
+  } else if (gv == 16) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) o[j] = pk_min(o[j], (uint32_t)__shfl_xor((int)o[j], 4));
+    const uint32_t v = (lane & 4) ? o[1] : o[0];
+    sz = scale_zero<B>(arena, lo_f(v), -hi_f(v));
+    put_meta(lane / lpg, lane & 7, sz);
+  } else {
+    sz = scale_zero<B>(arena, lo_f(o[0]), -hi_f(o[0]));
+    sz2 = scale_zero<B>(arena, lo_f(o[1]), -hi_f(o[1]));
+    put_meta(lane / lpg, lane & 3, sz);
+    put_meta(lane / lpg, 4 + (lane & 3), sz2);
   }
-  uint32_t v = (lane & 4) ? o[1] : o[0];
-  if (gv >= 64) v = join16(v, pk_min);
-  if (gv >= 128) v = join32(v, pk_min);
-  const uint32_t sz = scale_zero<B>(arena, lo_f(v), -hi_f(v));
-  const int row = lane >> 4, rpg = gv / 32, ng = kHeadDim / gv;
-  if ((lane & 15) < 8 && (row & (rpg - 1)) == 0) {
-    const int at = (row / rpg) * 32 + 8 * wv + (lane & 7);  // value_meta_s / value_meta_z
-    reinterpret_cast<uint16_t*>(vmb)[at] = (uint16_t)sz;
-    reinterpret_cast<uint16_t*>(vmb)[ng * 32 + at] = (uint16_t)(sz >> 16);
-  }
+  // a value that its group's lanes hold for token t, in every lane (v2: tokens
+  // 4-7 of groups of 8 channels)
+  auto of_token = [&](auto tc, uint32_t v, uint32_t v2) -> uint32_t {
+    constexpr int t = decltype(tc)::value;
+    if constexpr (!FINE) return dpp<kRowBcast + t>(v);
+    if (gv == 16) return (uint32_t)__shfl((int)v, (lane & ~7) + t);
+    return (uint32_t)__shfl((int)(t < 4 ? v : v2), (lane & ~3) + (t & 3));
+  };
   // codes of the two channels, element t of their operand words w0, w1
   uint32_t w0[2] = {0u, 0u}, w1[2] = {0u, 0u};
   if constexpr (B <= 2) {
-    Thresholds<B> own;
-    own.t[0] = threshold<0>(sz) * 0x10001u;
+    constexpr int NT = B == 1 ? 1 : 3;
+    uint32_t own[3], own2[3] = {0u, 0u, 0u};
+    own[0] = threshold<0>(sz) * 0x10001u;
     if constexpr (B == 2) {
-      own.t[1] = threshold<1>(sz) * 0x10001u;
-      own.t[2] = threshold<2>(sz) * 0x10001u;
+      own[1] = threshold<1>(sz) * 0x10001u;
+      own[2] = threshold<2>(sz) * 0x10001u;
+    }
+    if (FINE && gv == 8) {
+      own2[0] = threshold<0>(sz2) * 0x10001u;
+      if constexpr (B == 2) {
+        own2[1] = threshold<1>(sz2) * 0x10001u;
+        own2[2] = threshold<2>(sz2) * 0x10001u;
+      }
     }
     uint32_t acc = 0u;  // low half: the even channel, high half: the odd one
     for_tokens([&](auto tc) {
       constexpr int t = decltype(tc)::value;
       Thresholds<B> T;
 #pragma unroll
-      for (int k = 0; k < (B == 1 ? 1 : 3); ++k) T.t[k] = dpp<kRowBcast + t>(own.t[k]);
+      for (int k = 0; k < NT; ++k) T.t[k] = of_token(tc, own[k], own2[k]);
       add_codes<B>(x[t], T, B == 1 ? (t >> 1) + 4 * (t & 1) : 2 * t, acc);
     });
     if constexpr (B == 1) {  // pairs apart: elements 2i at bit i, 2i + 1 at bit 16 + i
@@ -421,7 +424,7 @@ __device__ __forceinline__ uint32_t value_block_matrix(uint8_t* arena, uint32_t 
   } else {
     for_tokens([&](auto tc) {
       constexpr int t = decltype(tc)::value;
-      const Grid g = grid_of(dpp<kRowBcast + t>(sz));
+      const Grid g = grid_of(of_token(tc, sz, sz2));
       constexpr int sh = B == 4 ? 4 * (t >> 1) + 16 * (t & 1) : 8 * (t & 3);
       w0[B == 8 ? t >> 2 : 0] |= quantize<B>(lo_f(x[t]), g) << sh;
       w1[B == 8 ? t >> 2 : 0] |= quantize<B>(hi_f(x[t]), g) << sh;
@@ -453,59 +456,19 @@ __device__ __forceinline__ uint32_t value_block_matrix(uint8_t* arena, uint32_t 
     *reinterpret_cast<uint2*>(o32 + (c16 + 16 * wv) * 16 + 2 * mb) = make_uint2(w0[0], w0[1]);
     *reinterpret_cast<uint2*>(o32 + (c16 + 1 + 16 * wv) * 16 + 2 * mb) = make_uint2(w1[0], w1[1]);
   }
-  const uint32_t s = sz & 0xFFFFu;
-  return s == 0x7E00u ? 0u : s;
+  const uint32_t s = sz & 0xFFFFu, s2 = sz2 & 0xFFFFu;
+  return max(s == 0x7E00u ? 0u : s, s2 == 0x7E00u ? 0u : s2);
 }
 
-// Values of one 32-token block, canonical layout: lane = channels 8*cc ..
-// 8*cc + 7 of the tokens t = 16*i + 4*wv + row.  vmb: the block's first meta.
-template <int B>
-__device__ __forceinline__ uint32_t value_block_rows(uint8_t* arena, u4_t (&x)[2], int gv, uint8_t* vcb,
-                                                     uint32_t* vmb, int lane, int wv) {
-  const int cc = lane & 15, row = lane >> 4, lpg = gv / 8, ng = kHeadDim / gv;
-  uint32_t most = 0u;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    uint32_t nan = 0u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) nan = probe_nan(x[i][k], nan);
-    uint32_t v = min_negmax(x[i][0]);
-#pragma unroll
-    for (int k = 1; k < 4; ++k) v = pk_min(v, min_negmax(x[i][k]));
-    if (__builtin_amdgcn_ballot_w64(has_nan(nan)) && has_nan(nan)) {
-      v = 0xFC007C00u;  // range +inf
-#pragma unroll
-      for (int k = 0; k < 4; ++k) x[i][k] = finite_or_zero(x[i][k]);
-    }
-    if (lpg >= 2) v = pk_min(v, dpp<dec::kQuadXor1>(v));
-    if (lpg >= 4) v = pk_min(v, dpp<dec::kQuadXor2>(v));
-    if (lpg >= 8) v = pk_min(v, dpp<dec::kHalfMirror>(v));
-    if (lpg >= 16) v = pk_min(v, dpp<dec::kMirror>(v));
-    const uint32_t sz = scale_zero<B>(arena, lo_f(v), -hi_f(v));
-    const int t = 16 * i + 4 * wv + row;
-    if ((cc & (lpg - 1)) == 0) vmb[(size_t)t * ng + cc / lpg] = sz;
-    if constexpr (B <= 2) {
-      Thresholds<B> T;
-      T.t[0] = threshold<0>(sz) * 0x10001u;
-      if constexpr (B == 2) {
-        T.t[1] = threshold<1>(sz) * 0x10001u;
-        T.t[2] = threshold<2>(sz) * 0x10001u;
-      }
-      uint32_t acc = 0u;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) add_codes<B>(x[i][m], T, 2 * B * m, acc);
-      store_row_bits<B>(acc, vcb + (size_t)t * 16 * B, cc);
-    } else {
-      const Grid g = grid_of(sz);
-      uint32_t c[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) c[e] = quantize<B>(e & 1 ? hi_f(x[i][e >> 1]) : lo_f(x[i][e >> 1]), g);
-      store8<B>(c, vcb + (size_t)t * 16 * B, cc);
-    }
-    const uint32_t s = sz & 0xFFFFu;
-    most = max(most, s == 0x7E00u ? 0u : s);
+template <bool FINE>
+__device__ __forceinline__ uint32_t quantize_values(const AppendArgs& a, int bv, uint32_t (&vx)[8], uint8_t* vcb,
+                                                    uint8_t* vmb, int lane, int wv) {
+  switch (bv) {
+    case 1: return value_block<1, FINE>(a.arena, vx, a.gv, vcb, vmb, lane, wv);
+    case 2: return value_block<2, FINE>(a.arena, vx, a.gv, vcb, vmb, lane, wv);
+    case 4: return value_block<4, FINE>(a.arena, vx, a.gv, vcb, vmb, lane, wv);
+    default: return value_block<8, FINE>(a.arena, vx, a.gv, vcb, vmb, lane, wv);
   }
-  return most;
 }
 
 template <int GK, bool AL>
@@ -523,15 +486,9 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
 #pragma unroll
   for (int i = 0; i < GK / 16; ++i) kx[i] = load8<AL>(rk.at(p0 + 16 * i + 4 * wv + row) + 8 * cc);
   uint32_t vx[8];
-  u4_t vr[2];
   auto load_v = [&](int b) {
-    if (a.matrix) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) vx[t] = load2<AL>(rv.at(p0 + 32 * b + value_token(wv, t)) + 2 * lane);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) vr[i] = load8<AL>(rv.at(p0 + 32 * b + 16 * i + 4 * wv + row) + 8 * cc);
-    }
+    for (int t = 0; t < 8; ++t) vx[t] = load2<AL>(rv.at(p0 + 32 * b + value_token(wv, t)) + 2 * lane);
   };
   load_v(0);
   uint32_t* bound = reinterpret_cast<uint32_t*>(blk + a.vb);
@@ -611,23 +568,8 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
     if (b > 0) load_v(b);
     uint8_t* vcb = seg + a.vc + (size_t)(t0 + 32 * b) * 16 * bv;
     uint8_t* vmb = seg + a.vm + (size_t)(t0 + 32 * b) * 4 * ng;
-    uint32_t s = 0u;
-    if (a.matrix) {
-      switch (bv) {
-        case 1: s = value_block_matrix<1>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
-        case 2: s = value_block_matrix<2>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
-        case 4: s = value_block_matrix<4>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
-        default: s = value_block_matrix<8>(a.arena, vx, a.gv, vcb, vmb, lane, wv); break;
-      }
-    } else {
-      uint32_t* vm32 = reinterpret_cast<uint32_t*>(vmb);
-      switch (bv) {
-        case 1: s = value_block_rows<1>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
-        case 2: s = value_block_rows<2>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
-        case 4: s = value_block_rows<4>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
-        default: s = value_block_rows<8>(a.arena, vr, a.gv, vcb, vm32, lane, wv); break;
-      }
-    }
+    const uint32_t s = a.gv >= 32 ? quantize_values<false>(a, bv, vx, vcb, vmb, lane, wv)
+                   : quantize_values<true>(a, bv, vx, vcb, vmb, lane, wv);
     most = max(most, s);
   }
   // the largest value scale raises the head's bound (decode sizes its weight
@@ -641,10 +583,10 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
   __syncthreads();
   uint8_t* kdst = seg + a.kc + (size_t)t0 * 16 * bk;
   switch (bk) {
-    case 1: key_codes<1, GK>(kx, par, a.matrix, kdst, lane, wv); break;
-    case 2: key_codes<2, GK>(kx, par, a.matrix, kdst, lane, wv); break;
-    case 4: key_codes<4, GK>(kx, par, a.matrix, kdst, lane, wv); break;
-    default: key_codes<8, GK>(kx, par, a.matrix, kdst, lane, wv); break;
+    case 1: key_codes<1, GK>(kx, par, kdst, lane, wv); break;
+    case 2: key_codes<2, GK>(kx, par, kdst, lane, wv); break;
+    case 4: key_codes<4, GK>(kx, par, kdst, lane, wv); break;
+    default: key_codes<8, GK>(kx, par, kdst, lane, wv); break;
   }
 }
 

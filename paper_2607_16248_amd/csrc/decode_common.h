@@ -1,6 +1,6 @@
-// Pieces shared by the decode kernels: wave reductions over DPP, the
-// online-softmax state of the vector path, and the combination of per-wave
-// partial results into one split record.
+// Pieces shared by the decode kernels: wave reductions over DPP, the mapping of
+// workgroups and rows, and the combination of per-wave partial results into
+// one split record.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -58,41 +58,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// floats per channel of the query rows staged for the vector passes
-template <int GQ>
-struct QStride {
-  static constexpr int value = GQ <= 4 ? GQ : GQ <= 8 ? 8 : 16;
-};
-
-template <int GQ>
-struct State {
-  float m[GQ];
-  float l[GQ];
-  float acc[GQ][8];
-};
-
-// Online-softmax update for one pass of 32 tokens held as sig (QK layout:
-// lanes 2t, 2t+1 hold token t).  Writes p to LDS, rescales the state.
-template <int GQ, bool CHUNK>
-__device__ __forceinline__ void softmax_pass(State<GQ>& st, float (&sig)[GQ], int half, int tl,
-                                             float* p_lds) {
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    const float mx = wave_max(sig[g]);
-    const float mnew = fmaxf(st.m[g], mx);
-    // a chunk row with no visible token yet keeps m = -inf: factor 1,
-    // weights 0 (single-token decode sees a token in every pass)
-    const bool none = CHUNK && mnew == -__builtin_inff();
-    const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(st.m[g] - mnew);
-    const float p = none ? 0.f : __builtin_amdgcn_exp2f(sig[g] - mnew);
-    st.l[g] = st.l[g] * alpha + (half ? 0.f : p);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) st.acc[g][k] *= alpha;
-    st.m[g] = mnew;
-    if (!half) p_lds[tl * GQ + g] = p;
-  }
 }
 
 // Locate this workgroup's (sequence, kv head, row group, split).
@@ -182,46 +147,12 @@ __device__ __forceinline__ int group_limit(const DecodeArgs& a, const DecodeSeq&
   return S.L - a.nqry + 1 + rg * a.qpr;
 }
 
-// (g0: the first row of the group the GQ rows start at; the chunk kernel
-// takes its fp16 tail in parts of 8 rows)
-template <int GQ>
-__device__ __forceinline__ void row_limits(const DecodeArgs& a, const DecodeSeq& S, int h, int rg, int (&lim)[GQ],
-                                           int g0 = 0) {
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) lim[g] = row_limit(a, S, rg, g0 + g);
-}
-
 // Per-wave partial results of GQ query heads, staged for the combine.
 template <int GQ>
 struct Reduce {
   float m[kWaves][GQ], l[kWaves][GQ];
   float acc[kWaves][GQ * kHeadDim];
 };
-
-// Vector-path state (lanes (tq, cc) hold 8 channels for a quarter of the
-// tokens; l is spread over lanes) into the staging area of wave wv.
-template <int GQ>
-__device__ __forceinline__ void stage_state(State<GQ>& st, Reduce<GQ>& r, int lane, int wv) {
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    st.l[g] = wave_sum(st.l[g]);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      st.acc[g][k] += __shfl_xor(st.acc[g][k], 16);
-      st.acc[g][k] += __shfl_xor(st.acc[g][k], 32);
-    }
-  }
-  if (lane < 16) {
-#pragma unroll
-    for (int g = 0; g < GQ; ++g)
-#pragma unroll
-      for (int k = 0; k < 8; ++k) r.acc[wv][g * kHeadDim + lane * 8 + k] = st.acc[g][k];
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int g = 0; g < GQ; ++g) { r.m[wv][g] = st.m[g]; r.l[wv][g] = st.l[g]; }
-  }
-}
 
 // After a barrier: merge the waves' partial results and write the record of
 // split sp for the GQ query heads of kv head h.
@@ -248,30 +179,6 @@ __device__ __forceinline__ void write_record(const DecodeArgs& a, const DecodeSe
     float* rec = a.ws + ((size_t)(S.ws_base + sp) * rows + rec_row<GQ, CHUNK>(a, h, rg, g0 + g)) * kRecFloats;
     rec[4 + c] = val;
     if (c == 0) { rec[0] = M; rec[1] = lsum; }
-  }
-}
-
-template <int GQ>
-__device__ __forceinline__ void init_state(State<GQ>& st) {
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    st.m[g] = -__builtin_inff();
-    st.l[g] = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) st.acc[g][k] = 0.f;
-  }
-}
-
-// This lane's two channels (2*lane, 2*lane+1) of the GQ query heads,
-// pre-scaled to base 2.
-template <int GQ, bool CHUNK>
-__device__ __forceinline__ void load_q_scaled(const DecodeArgs& a, const DecodeSeq& S, int h, int rg, int lane,
-                                              float (&qs0)[GQ], float (&qs1)[GQ], int g0 = 0) {
-#pragma unroll
-  for (int g = 0; g < GQ; ++g) {
-    const uint32_t w = reinterpret_cast<const uint32_t*>(a.q + q_index<GQ, CHUNK>(a, S, h, rg, g0 + g) * kHeadDim)[lane];
-    qs0[g] = h2f(w & 0xFFFF) * a.qscale;
-    qs1[g] = h2f(w >> 16) * a.qscale;
   }
 }
 

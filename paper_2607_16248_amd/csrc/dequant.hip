@@ -14,13 +14,8 @@ __device__ __forceinline__ float h2f(uint32_t bits16) {
   return (float)__builtin_bit_cast(_Float16, (uint16_t)bits16);
 }
 
-__device__ __forceinline__ uint32_t code_at(const uint8_t* row, int c, int bits) {
-  const int bit = c * bits;
-  return ((uint32_t)row[bit >> 3] >> (bit & 7)) & ((1u << bits) - 1u);
-}
-
-// Code of channel c from a matrix-layout key row / value block.
-__device__ __forceinline__ uint32_t key_code_matrix(const uint8_t* row, int c, int bits) {
+// Code of channel c from a key row / value block.
+__device__ __forceinline__ uint32_t key_code(const uint8_t* row, int c, int bits) {
   uint32_t code = 0;
   for (int p = 0; p < bits; ++p) {
     const BitLoc b = key_bit(c, p, bits);
@@ -29,7 +24,7 @@ __device__ __forceinline__ uint32_t key_code_matrix(const uint8_t* row, int c, i
   return code;
 }
 
-__device__ __forceinline__ uint32_t value_code_matrix(const uint8_t* block, int r, int c, int bits) {
+__device__ __forceinline__ uint32_t value_code(const uint8_t* block, int r, int c, int bits) {
   uint32_t code = 0;
   for (int p = 0; p < bits; ++p) {
     const BitLoc b = value_bit(r, c, p, bits);
@@ -48,20 +43,15 @@ __global__ __launch_bounds__(128) void dequant_kernel(DequantArgs a) {
     const uint8_t* seg = a.arena + packed_seg(a.pm, a.head0, a.head_stride, a.seq, h, p, q);
     const uint16_t* km = reinterpret_cast<const uint16_t*>(seg + a.km) + (size_t)(q / a.gk) * 2 * kHeadDim;
     const uint8_t* krow = seg + a.kc + (size_t)q * 16 * a.bk;
-    const uint32_t kcode = a.matrix ? key_code_matrix(krow, c, a.bk) : code_at(krow, c, a.bk);
+    const uint32_t kcode = key_code(krow, c, a.bk);
     kv = fmaf((float)kcode, h2f(km[c]), h2f(km[kHeadDim + c]));
     const int ng = kHeadDim / a.gv, g = c / a.gv;
-    if (a.matrix) {
-      const uint8_t* vblk = seg + a.vc + (size_t)(q / 32) * 512 * a.bv;
-      const uint8_t* vmb = seg + a.vm + (size_t)(q / 32) * 128 * ng;
-      const int r = q % 32;
-      const uint32_t vcode = value_code_matrix(vblk, r, c, a.bv);
-      vv = fmaf((float)vcode, h2f(*reinterpret_cast<const uint16_t*>(vmb + value_meta_s(g, r))),
-                h2f(*reinterpret_cast<const uint16_t*>(vmb + value_meta_z(g, r, ng))));
-    } else {
-      const uint32_t meta = reinterpret_cast<const uint32_t*>(seg + a.vm)[(size_t)q * ng + g];
-      vv = fmaf((float)code_at(seg + a.vc + (size_t)q * 16 * a.bv, c, a.bv), h2f(meta & 0xFFFF), h2f(meta >> 16));
-    }
+    const uint8_t* vblk = seg + a.vc + (size_t)(q / 32) * 512 * a.bv;
+    const uint8_t* vmb = seg + a.vm + (size_t)(q / 32) * 128 * ng;
+    const int r = q % 32;
+    vv = fmaf((float)value_code(vblk, r, c, a.bv),
+              h2f(*reinterpret_cast<const uint16_t*>(vmb + value_meta_s(g, r))),
+              h2f(*reinterpret_cast<const uint16_t*>(vmb + value_meta_z(g, r, ng))));
   } else {
     const size_t slot = (size_t)(p % a.W) * kHeadDim + c;
     kv = h2f(reinterpret_cast<const uint16_t*>(blk + a.tk)[slot]);
@@ -87,7 +77,7 @@ __device__ __forceinline__ uint32_t spread(uint32_t x) {
   }
 }
 
-// Canonical dword w of a key row from the row's matrix-layout dwords: per 8
+// Canonical dword w of a key row from the row's dwords: per 8
 // channels (operand block kb, lane group g) the even elements sit below the
 // odd ones, 16 bits apart (kvq_layout.h, key_bit).
 template <int B>
@@ -164,22 +154,16 @@ __global__ __launch_bounds__(256) void export_kernel(ExportArgs a) {
   if ((32 * b) % a.gk == 0 && tid < 128)  // a key group's scales and zeros: 512 bytes
     reinterpret_cast<uint32_t*>(a.km_out)[(size_t)(32 * b / a.gk) * 128 + tid] =
         reinterpret_cast<const uint32_t*>(seg + a.km)[(size_t)(t / a.gk) * 128 + tid];
-  if (a.matrix) {
-    for (int i = tid; i < 32 * BV; i += 256) reinterpret_cast<uint4*>(vblk)[i] = reinterpret_cast<const uint4*>(vc)[i];
-    for (int i = tid; i < 128 * BK; i += 256) kc_out[i] = canonical_key<BK>(kc + i / (4 * BK) * (4 * BK), i % (4 * BK));
-    for (int i = tid; i < 32 * ng; i += 256) {
-      const int r = i / ng, g = i % ng;
-      const uint32_t s = *reinterpret_cast<const uint16_t*>(vm + value_meta_s(g, r));
-      const uint32_t z = *reinterpret_cast<const uint16_t*>(vm + value_meta_z(g, r, ng));
-      vm_out[i] = s | (z << 16);
-    }
-    __syncthreads();
-    for (int i = tid; i < 128 * BV; i += 256) vc_out[i] = canonical_value<BV>(vblk, i / (4 * BV), i % (4 * BV));
-  } else {
-    for (int i = tid; i < 128 * BK; i += 256) kc_out[i] = kc[i];
-    for (int i = tid; i < 128 * BV; i += 256) vc_out[i] = vc[i];
-    for (int i = tid; i < 32 * ng; i += 256) vm_out[i] = reinterpret_cast<const uint32_t*>(vm)[i];
+  for (int i = tid; i < 32 * BV; i += 256) reinterpret_cast<uint4*>(vblk)[i] = reinterpret_cast<const uint4*>(vc)[i];
+  for (int i = tid; i < 128 * BK; i += 256) kc_out[i] = canonical_key<BK>(kc + i / (4 * BK) * (4 * BK), i % (4 * BK));
+  for (int i = tid; i < 32 * ng; i += 256) {
+    const int r = i / ng, g = i % ng;
+    const uint32_t s = *reinterpret_cast<const uint16_t*>(vm + value_meta_s(g, r));
+    const uint32_t z = *reinterpret_cast<const uint16_t*>(vm + value_meta_z(g, r, ng));
+    vm_out[i] = s | (z << 16);
   }
+  __syncthreads();
+  for (int i = tid; i < 128 * BV; i += 256) vc_out[i] = canonical_value<BV>(vblk, i / (4 * BV), i % (4 * BV));
 }
 
 template <int BK>

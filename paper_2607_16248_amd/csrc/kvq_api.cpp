@@ -36,7 +36,7 @@ struct kvq_cache {
   std::vector<uint64_t> head0;
   std::vector<HeadLayout> lay;
   std::vector<int32_t> L, Lq;
-  std::vector<uint8_t> matrix;  // 1: matrix layout and the matrix-core decode kernel
+  std::vector<uint8_t> matrix;  // 1: the kernels of decode_mfma.hip (else decode_exact.hip)
   std::vector<int> occupancy;    // resident decode workgroups per compute unit, per sequence's kernel
   int32_t split_tokens = 0;
   // paged layout: block table on the device (pm.table), page lists and the
@@ -481,7 +481,6 @@ kvq_status kvq_append(kvq_cache* c, const void* K, const void* V, int32_t n_max,
       a.vm = (uint32_t)lay.vm; a.tk = (uint32_t)lay.tk; a.tv = (uint32_t)lay.tv; a.vb = (uint32_t)lay.vb;
       a.n_max = n_max; a.hkv = d.num_kv_heads; a.gk = d.key_group; a.gv = d.value_group; a.W = c->W;
       a.quantize = quant ? 1 : 0;
-      a.matrix = c->matrix[cls.second[0]];
       a.pm = c->pm;
       int wg = 0, n = 0;
       for (int i : cls.second) {
@@ -526,9 +525,8 @@ struct Rows {
 };
 
 // Single-token decode: one row group of the kv head's query heads.  Chunk
-// queries on the vector kernel: the largest of its row groups (8, 5, 4, 2,
-// 1 rows) made of whole queries, with a whole number of groups.  On the
-// matrix cores (32 rows in the chunk kernel for 1- and 2-bit classes, 16 for
+// queries of the classes of decode_exact.hip: groups of 16 rows.  Of the others
+// (32 rows in the chunk kernel for 1- and 2-bit classes, 16 for
 // those and 4-bit classes, with value groups of 32 channels; 8, 5 or 4 in
 // the decode kernel), the row group of whole queries with the smallest
 // estimated time: ceil(nqry / qpr) passes over the kv head's cache at a
@@ -547,17 +545,10 @@ Rows rows_for(const kvq_cache* c, bool matrix, int nqry, int bk, int bv) {
   r.rows = gqh;
   if (nqry <= 1) return r;
   r.nqry = nqry;
-  if (!matrix) {
-    for (int rg : {8, 5, 4, 2, 1}) {
-      if (rg % gqh == 0 && nqry % (rg / gqh) == 0) {
-        r.qpr = rg / gqh;
-        r.nrg = nqry / r.qpr;
-        r.rows = rg;
-        return r;
-      }
-    }
-    r.qpr = 1;  // not reached: rg = gqh always qualifies
-    r.nrg = nqry;
+  if (!matrix) {  // one tile of 16 rows holds whole queries; the rest are spare
+    r.rows = 16;
+    r.qpr = 16 / gqh;
+    r.nrg = (nqry + r.qpr - 1) / r.qpr;
     return r;
   }
   const bool rows16 = c->d.value_group == 32 && bk + bv <= 8;
@@ -944,7 +935,6 @@ kvq_status kvq_dequant(const kvq_cache* c, int32_t seq, int32_t tok0, int32_t nt
   a.vm = (uint32_t)lay.vm; a.tk = (uint32_t)lay.tk; a.tv = (uint32_t)lay.tv;
   a.hkv = c->d.num_kv_heads; a.gk = c->d.key_group; a.gv = c->d.value_group; a.W = c->W;
   a.bk = c->bk[seq]; a.bv = c->bv[seq]; a.Lq = c->Lq[seq]; a.tok0 = tok0; a.ntok = ntok;
-  a.matrix = c->matrix[seq];
   const int e = kvq::launch_dequant(a, stream);
   if (e) return hip_fail(e, "dequant launch");
   return ok();
@@ -980,7 +970,7 @@ kvq_status kvq_export(const kvq_cache* c, int32_t seq, int32_t h, void* dst, siz
   x.kc = (uint32_t)lay.kc; x.km = (uint32_t)lay.km; x.vc = (uint32_t)lay.vc;
   x.vm = (uint32_t)lay.vm; x.tk = (uint32_t)lay.tk; x.tv = (uint32_t)lay.tv;
   x.bk = c->bk[seq]; x.bv = c->bv[seq]; x.gk = c->d.key_group; x.gv = c->d.value_group; x.W = c->W;
-  x.Lq = (int32_t)Lq; x.ntail = (int32_t)tail; x.matrix = c->matrix[seq]; x.seq = seq; x.h = h;
+  x.Lq = (int32_t)Lq; x.ntail = (int32_t)tail; x.seq = seq; x.h = h;
   x.pm = c->pm;
   const int e = kvq::launch_export(x, stream);
   if (e) return hip_fail(e, "export launch");

@@ -3,18 +3,17 @@
 // Device arena:
 //   [0, 256)            header; word 0 is the sticky error flag
 //   per sequence i, per kv head h, one block of head_stride(i) bytes:
-//     kc  key codes    [Cq][16*bk]       token rows, canonical bit order
+//     kc  key codes    [Cq][16*bk]       token rows
 //     km  key meta     [Cq/Gk][2][128]   fp16 scales then zeros per key group
-//     vc  value codes  [Cq][16*bv]
-//     vm  value meta   [Cq][128/Gv][2]   fp16 (scale, zero) per value group
+//     vc  value codes  [Cq][16*bv]       blocks of 32 tokens
+//     vm  value meta   [Cq][128/Gv][2]   fp16 scales and zeros, blocks of 32 tokens
 //     tk  key ring     [W][128]          fp16 tokens not yet packed
 //     tv  value ring   [W][128]
 //   Cq = Gk * floor(max(0, L_max - R) / Gk) is the most tokens ever packed;
 //   W = R + Gk ring slots hold the < R + Gk fp16 tokens, token p in slot p % W.
 //   Every region starts on a 256-byte boundary.
 //
-// The packed regions use the canonical byte order of the export image, so an
-// export is a handful of device-to-device copies.
+// kvq_layout.h has the order of the codes and of the value meta.
 #pragma once
 
 #include <stddef.h>
@@ -123,7 +122,6 @@ struct AppendArgs {
   uint32_t kc, km, vc, vm, tk, tv, vb;
   int32_t n_max, hkv, gk, gv, W, nseq, total_wg;
   int32_t quantize;   // 1: pack groups in this launch
-  int32_t matrix;     // 1: matrix layout (kvq_layout.h) for this bit class
   PageMap pm;
   AppendSeq seq[kMaxSeqPerLaunch];
 };
@@ -225,15 +223,15 @@ struct DequantArgs {
   uint64_t head_stride;
   uint32_t kc, km, vc, vm, tk, tv;
   int32_t hkv, gk, gv, W, bk, bv, Lq, tok0, ntok;
-  int32_t matrix, seq;
+  int32_t seq;
   PageMap pm;
 };
 
 // ---------------------------------------------------------------- export
 
 // The canonical image of one (seq, head): packed codes and meta of 32-token
-// blocks [0, Lq / 32) (re-ordered from the matrix layout, or copied), then the
-// fp16 tail's rows in token order.
+// blocks [0, Lq / 32) re-ordered from the device layout, then the fp16 tail's
+// rows in token order.
 struct ExportArgs {
   const uint8_t* arena;
   uint64_t head0;       // (seq, head 0) block (paged: the sequence's ring region)
@@ -245,7 +243,7 @@ struct ExportArgs {
   uint8_t* tk_out;      // key tail [ntail][128] fp16
   uint8_t* tv_out;      // value tail [ntail][128] fp16
   uint32_t kc, km, vc, vm, tk, tv;
-  int32_t bk, bv, gk, gv, W, Lq, ntail, matrix, seq, h;
+  int32_t bk, bv, gk, gv, W, Lq, ntail, seq, h;
   PageMap pm;
 };
 
@@ -261,12 +259,13 @@ struct WordReset {
 int launch_word_reset(const WordReset& r, void* stream);
 int launch_decode(const DecodeArgs& a, int bk, int bv, int gq, void* stream);
 int launch_decode_matrix(const DecodeArgs& a, int bk, int bv, int gq, void* stream);
-// Matrix-core decode (and the matrix layout) for this bit class: 4, 5 or 8
-// query heads per kv head, 1- or 2-bit codes, value groups >= 32 channels,
-// and a (sequence, head) block that one buffer resource covers.
+// Whether the decode kernels of decode_mfma.hip serve this class: 1- and 2-bit
+// or 4- and 8-bit keys and values, value groups >= 32 channels, and a
+// (sequence, head) block that one buffer resource covers; decode_exact.hip
+// serves every other.
 bool matrix_decode_supported(int bk, int bv, int gq, int gk, int gv, uint64_t head_bytes);
-// Waves per SIMD of the matrix-core kernel for this bit class (2, 3 or 4);
-// the vector kernel runs two.
+// Waves per SIMD of that kernel for this bit class (2, 3 or 4); the others run
+// two.
 int matrix_decode_occupancy(int bk, int bv, int gk, int gq);
 // Chunk queries over row groups of 16 or 32 rows (chunk_mfma.hip).
 int launch_chunk_matrix(const DecodeArgs& a, int bk, int bv, int rows, void* stream);
@@ -279,6 +278,9 @@ int launch_prefill(const DecodeArgs& a, int bk, int bv, void* stream);
 // object per class); launch_decode_matrix (matrix_dispatch.cpp) picks one.
 template <int BK, int BV>
 int launch_matrix_class(const DecodeArgs& a, int gq, void* stream);
+// The classes those kernels don't take, by key bits (decode_exact.hip).
+template <int BK>
+int launch_exact_class(const DecodeArgs& a, int bv, void* stream);
 int launch_export(const ExportArgs& a, void* stream);
 int launch_merge(const MergeArgs& a, void* stream);
 int launch_dgap(const struct DgapArgs& a, int batch, void* stream);

@@ -1,12 +1,7 @@
-// Device bit layouts of the packed codes.
+// Device bit layout of the packed codes.  (The export image has its own, the
+// canonical order: code rows of 16*b bytes per token, channel c at row bits
+// [c*b, c*b + b); value meta [t][128/Gv][(s, z)].)
 //
-// Two layouts exist per sequence, chosen when the cache is created:
-//
-//  canonical  key and value code rows of 16*b bytes per token, channel c at
-//             row bits [c*b, c*b + b); value meta [t][128/Gv][(s, z)].
-//             This is also the export image's order.
-//
-//  matrix     (caches read by the matrix-core decode kernel)
 //    The codes one lane of a 16x16x32 MFMA operand needs (8 elements) sit
 //    together in the lane's dwords, placed so that a few shifts and ANDs, a
 //    byte permute or a table lookup turn them into the operand's halves.
@@ -39,7 +34,7 @@
 //      total as the canonical [t][g][(s, z)] order.  pos = tau^-1 puts the 8
 //      tokens of K-group kg (lanes 16*kg .. 16*kg + 15) in 16 contiguous bytes,
 //      in B-fragment element order.
-//    key meta is [group][s[128], z[128]] in both layouts.
+//    key meta is [group][s[128], z[128]], as in the export image.
 #pragma once
 
 #include <stdint.h>
@@ -52,7 +47,7 @@
 
 namespace kvq {
 
-// Which caches the matrix-core decode kernel serves: 1- or 2-bit keys and
+// Which caches the kernels of decode_mfma.hip serve: 1- or 2-bit keys and
 // values in any combination, or 4- or 8-bit keys and values in any
 // combination; 1, 2, 4, 5 or 8 query heads per kv head (1 and 2 in the
 // four-head layout with empty heads); value groups of at least 32 channels.

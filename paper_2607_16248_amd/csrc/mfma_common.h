@@ -103,6 +103,25 @@ __device__ __forceinline__ f4_t mfma(h8_t a, h8_t b, f4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
+// Subnormal operands lose low bits of their products (see unpack_bits): an
+// operand of raw fp16 numbers is lifted by 2^12, out of the subnormal range,
+// while every number it has met in the wave is below 8.  raw: set for good by
+// the first larger one; the caller then takes 2^-12 out of its accumulators.
+constexpr float kLift = 4096.f;
+__device__ __forceinline__ bool needs_raw(u4_t w) {
+  typedef uint16_t us2_t __attribute__((ext_vector_type(2)));
+  us2_t m = {0, 0};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) m = __builtin_elementwise_max(m, __builtin_bit_cast(us2_t, w[t] & 0x7FFF7FFFu));
+  return __builtin_amdgcn_ballot_w64(m.x >= 0x4800u || m.y >= 0x4800u) != 0;  // 8.0
+}
+__device__ __forceinline__ h8_t lifted(u4_t w, bool raw) {
+  const _Float16 f = (_Float16)(raw ? 1.f : kLift);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) w[t] = h2u(u2h(w[t]) * (h2_t){f, f});
+  return __builtin_bit_cast(h8_t, w);
+}
+
 // Buffer resource over one (sequence, kv head) block.  Every load is
 // base + per-lane offset + uniform offset: the per-block part is scalar
 // arithmetic and the vector ALU does no address math.  The host keeps the

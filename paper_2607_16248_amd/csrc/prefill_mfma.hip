@@ -48,6 +48,7 @@
 #include "kvq_internal.h"
 #include "kvq_layout.h"
 #include "mfma_common.h"
+#include "scaled_ops.h"
 
 namespace kvq {
 namespace {
@@ -63,71 +64,6 @@ constexpr int kZRow = 132;          // dwords per staged key group: s[128], z[12
 constexpr float kTop = 14.f;        // weights stay below 2^14 ...
 constexpr float kHeadroom = 6.f;    // ... a new reference puts the largest at 2^8
 constexpr float kNoScore = -1e30f;  // below any score
-
-// what one bit width's operands look like
-template <int B>
-struct Code {
-  static constexpr int parts = B <= 2 ? 1 : 2;                       // fp16 parts of an operand
-  static constexpr float c0 = B == 1 ? 0.5f : B == 2 ? 1.f : B == 4 ? 8.f : 128.f;
-  static constexpr float unit = B == 1 ? -0.5f : 2.f;                // code term = unit * operand sum
-  static constexpr int reach = B <= 2 ? 0 : B == 4 ? 2 : 6;          // |operand| <= 2^reach * s
-};
-
-// (code - c0) / 2 * 2^X of a pair whose codes sit at the bits stated below;
-// f holds 2^X (or 2^(X-1)) twice.
-__device__ __forceinline__ h2_t half_codes2(uint32_t y, h2_t f) {  // bits 8-9 of each half: 2 + code / 2
-  return __builtin_elementwise_fma(u2h((y & 0x03000300u) | 0x40004000u), f, f * (h2_t){(_Float16)-2.5f, (_Float16)-2.5f});
-}
-__device__ __forceinline__ h2_t half_codes4(uint32_t y, h2_t f) {  // bits 0-3 of each half: 1024 + code
-  return (u2h((y & 0x000F000Fu) | 0x64006400u) - (h2_t){(_Float16)1032.f, (_Float16)1032.f}) * f;
-}
-__device__ __forceinline__ h2_t half_codes8(uint32_t x, int pair, h2_t f) {  // bytes 2 * pair, 2 * pair + 1
-  const h2_t h = u2h(__builtin_amdgcn_perm(0x64646464u, x, pair ? 0x04030402u : 0x04010400u));
-  return (h - (h2_t){(_Float16)1152.f, (_Float16)1152.f}) * f;
-}
-__device__ __forceinline__ void put_product(h2_t c, uint32_t s, uint32_t& hi, uint32_t& lo) {
-  const h2_t h = c * u2h(s);
-  hi = h2u(h);
-  lo = h2u(__builtin_elementwise_fma(c, u2h(s), -h));
-}
-
-// Operand parts of 8 elements.  x: the lane's packed dwords of the operand;
-// s: the elements' scales; at: where the codes sit (1 bit: pair t at bits at
-// + t, +16; 2-bit keys: pair t at 2t, 2t + 16 of x >> at; 2-bit values:
-// element e at 2e of x >> at); f: the operand's power of two (two bits: 2^X,
-// else 2^(X-1); one bit: 2^X).
-template <int B, bool VALUE>
-__device__ __forceinline__ void unpack_scaled(const uint32_t (&x)[2], u4_t s, int at, h2_t f, u4_t& hi, u4_t& lo) {
-  if constexpr (B == 1) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      hi[t] = ((x[0] << (15 - at - t)) & 0x80008000u) | (VALUE ? h2u(u2h(s[t]) * f) : s[t]);
-  } else if constexpr (B == 2 && !VALUE) {
-    const uint32_t y = x[0] >> at;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) hi[t] = h2u(half_codes2(y << (8 - 2 * t), f) * u2h(s[t]));
-  } else if constexpr (B == 2) {
-    const uint32_t v = (x[0] >> at) & 0xFFFFu, y = v | (v << 14);  // element pair t at 4t, 4t + 16
-#pragma unroll
-    for (int t = 0; t < 4; ++t) hi[t] = h2u(half_codes2(t < 2 ? y << (8 - 4 * t) : y >> (4 * t - 8), f) * u2h(s[t]));
-  } else if constexpr (B == 4) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      uint32_t h, l;
-      put_product(half_codes4(x[0] >> (4 * t), f), s[t], h, l);
-      hi[t] = h;
-      lo[t] = l;
-    }
-  } else {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      uint32_t h, l;
-      put_product(half_codes8(x[t >> 1], t & 1, f), s[t], h, l);
-      hi[t] = h;
-      lo[t] = l;
-    }
-  }
-}
 
 // q and out need no more than their element's alignment
 typedef u4_t u4_any __attribute__((aligned(4)));
@@ -204,17 +140,8 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
   }
 
-  // the value shift: |V'| < 2^15 for the head's largest scale
-  // (and every factor of V' a finite half: 2.5 * 2^X, 2^reach * 2^X)
-  constexpr int kMaxX = (BV == 2 ? 13 : 15) - Code<BV>::reach;
-  int X = kMaxX;
-  if (vbits != 0u) {
-    int ex = 0;
-    frexpf(h2f(vbits), &ex);
-    X = min(kMaxX, 15 - ex - Code<BV>::reach);
-  }
-  const _Float16 xf = (_Float16)ldexpf(1.f, BV > 2 ? X - 1 : X), kf = (_Float16)(BK > 2 ? 0.5f : 1.f);
-  const h2_t vfac = {xf, xf}, kfac = {kf, kf};
+  const int X = value_shift<BV>(vbits);
+  const h2_t vfac = operand_factor<BV>(X), kfac = operand_factor<BK>(0);
   const float unit_packed = Code<BV>::unit * ldexpf(1.f, -X);
 
   // this wave's operands: keys, 16-token tile kmb and channel block kkb;

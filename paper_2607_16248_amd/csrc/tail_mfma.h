@@ -100,6 +100,7 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
     return r;
   };
 
+  bool raw[8] = {};  // per tile of 16 channels: its values enter lifted while they are small
   for (int b = wv; 32 * b < ntail; b += kWaves) {
     // scores: tokens 32b + 16mb + 4blk + r of row 16u + col
     f4_t d[NT][2];
@@ -158,15 +159,23 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
       u4_t w;
 #pragma unroll
       for (int e = 0; e < 4; ++e) w[e] = (uint32_t)vr[2 * e][16 * t] | ((uint32_t)vr[2 * e + 1][16 * t] << 16);
+      if (!raw[t] && mfma_ops::needs_raw(w)) {
+        raw[t] = true;
+#pragma unroll
+        for (int u = 0; u < NT; ++u) st.acc[u][t] *= 1.f / mfma_ops::kLift;
+      }
+      const h8_t v8 = mfma_ops::lifted(w, raw[t]);
 #pragma unroll
       for (int u = 0; u < NT; ++u) {
-        st.acc[u][t] = mfma_ops::mfma(__builtin_bit_cast(h8_t, w), ph[u], st.acc[u][t]);
-        st.acc[u][t] = mfma_ops::mfma(__builtin_bit_cast(h8_t, w), pl[u], st.acc[u][t]);
+        st.acc[u][t] = mfma_ops::mfma(v8, ph[u], st.acc[u][t]);
+        st.acc[u][t] = mfma_ops::mfma(v8, pl[u], st.acc[u][t]);
       }
     }
   }
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) st.acc[u][t] *= raw[t] ? 1.f : 1.f / mfma_ops::kLift;
     st.l[u] += __shfl_xor(st.l[u], 16);
     st.l[u] += __shfl_xor(st.l[u], 32);
   }

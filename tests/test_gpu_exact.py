@@ -1,0 +1,74 @@
+"""GPU parity of the decode kernel of the mixed and fine-grouped classes (1- or
+2-bit keys with 4- or 8-bit values and the reverse, value groups of 8 or 16
+channels) against the fp64 oracle: every such class and value group, key
+groups of 32 to 128 tokens (zero-point terms per group), all head counts,
+chunk rows that fill a tile of 16 and that leave spare rows and queries,
+pages, ragged batches, and value scales and key ranges at both ends of fp16.
+
+Bound: q, keys and values are exact operands and weights carry 22 bits, so a
+row is off by the fp32 sums alone: 2^-24 per addition over up to 2^10 blocks
+of partial sums and scores of magnitude up to 2^5 (an absolute score error of
+2^-19 is a relative weight error of 2^-19): 2^-17 in all."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import Case, log, row_rel_err
+from workloads import Workload, gen_q_chunk
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+TOL = 2.0 ** -17
+
+
+def W(gq, lens, bk, bv, gk=32, gv=32, R=0):
+    n = len(lens)
+    return Workload(f"exact_gq{gq}_K{bk}V{bv}_gk{gk}_gv{gv}_R{R}", n, 2 * gq, 2, 128, lens, (bk,) * n, (bv,) * n, gk, gv, R,
+                    cfg_id=97)
+
+
+CLASSES = [(1, 4, 32), (1, 8, 128), (2, 4, 64), (2, 8, 32), (4, 1, 32), (4, 2, 64), (8, 1, 32), (8, 2, 128), (1, 1, 16),
+           (2, 2, 8), (4, 4, 16), (8, 8, 8), (1, 2, 8), (4, 8, 8), (8, 4, 16), (2, 8, 16)]
+
+
+@pytest.mark.parametrize("i", range(len(CLASSES)), ids=[f"K{k}V{v}_gv{g}" for k, v, g in CLASSES])
+def test_decode(i):
+    bk, bv, gv = CLASSES[i]
+    w = W((4, 5, 8, 1, 2)[i % 5], (1111, 64 + 32 * i), bk, bv, (32, 64, 128)[i % 3], gv, (0, 37, 128)[i % 3])
+    c = Case(w, **({"page_tokens": 128} if i % 4 == 1 else {}))
+    c.append_all((700, 411))
+    out = c.decode()
+    for s in range(2):
+        err = row_rel_err(out[s], c.oracle_out(s)).max()
+        log(f"[exact] {w.name} seq {s}: {err:.2e}")
+        assert err <= TOL, s
+
+
+@pytest.mark.parametrize("gq,bk,bv,gk,gv,n_q,R", [(4, 4, 2, 32, 32, 4, 0), (4, 2, 8, 64, 32, 5, 20), (5, 1, 4, 32, 16, 7, 0),
+                                                  (8, 8, 1, 128, 8, 3, 64), (1, 2, 2, 32, 8, 17, 0), (2, 4, 4, 64, 16, 9, 300)])
+def test_chunk_rows(gq, bk, bv, gk, gv, n_q, R):
+    w = W(gq, (700,), bk, bv, gk, gv, R)
+    c = Case(w)
+    c.append_all()
+    q = gen_q_chunk(w, n_q)
+    out = c.cache.chunk(torch.from_numpy(q[None]).cuda())[0].cpu().numpy()
+    err = row_rel_err(out, oracle.chunk_seq(q, c.K[0], c.V[0], bk, bv, gk, gv, R)).max()
+    log(f"[exact] {w.name} n_q {n_q}: {err:.2e}")
+    assert err <= TOL
+
+
+@pytest.mark.parametrize("bk,bv,gv", [(1, 8, 32), (8, 1, 32), (2, 2, 16), (4, 2, 8), (1, 4, 16)])
+@pytest.mark.parametrize("scale", [2.0 ** -20, 3000.0])
+def test_ranges(bk, bv, gv, scale):
+    """Value scales down to single subnormal steps and up to the largest; key groups that span +-30000."""
+    w = W(4, (600,), bk, bv, 32, gv)
+    c = Case(w)
+    c.V[0] = np.clip(c.V[0].astype(np.float32) * scale, -60000, 60000).astype(np.float16)
+    if scale > 1:
+        c.K[0][:, :, 5] = np.where(np.arange(600) % 2 == 0, 30000, -30000).astype(np.float16)[:, None]
+        c.q[0][:, 5] = (c.q[0][:, 5].astype(np.float32) * 1e-4).astype(np.float16)
+        c.qd = torch.from_numpy(np.stack(c.q)).cuda()
+    c.append_all()
+    err = row_rel_err(c.decode()[0], c.oracle_out(0)).max()
+    log(f"[exact] {w.name} scale {scale:g}: {err:.2e}")
+    assert err <= TOL

@@ -69,3 +69,17 @@ def test_chunk_rows(gq, bits, n_q, L, R):
     err = row_rel_err(out, ref).max()
     log(f"[tail] {c.w.name} n_q {n_q}: {err:.2e}")
     assert err <= (2.0 ** -20 * 4 if L <= R else ATTN_TOL)
+
+
+@pytest.mark.parametrize("gq,bits", [(4, (1, 1)), (5, (2, 2)), (8, (4, 1))])
+@pytest.mark.parametrize("scale,big", [(2.0 ** -20, 0), (2.0 ** -20, 77), (1e4, 0)])
+def test_value_ranges(gq, bits, scale, big):
+    """Values down to subnormal fp16, alone and with one large token far into the tail, and large ones."""
+    c = Case(W(150, gq, bits[0], bits[1], 150))
+    c.V[0] = np.clip(c.V[0].astype(np.float32) * scale, -60000, 60000).astype(np.float16)
+    if big:
+        c.V[0][big] = (c.V[0][big].astype(np.float32) * 2.0 ** 26).astype(np.float16)
+    c.append_all()
+    err = row_rel_err(c.decode()[0], c.oracle_out(0)).max()
+    log(f"[tail] {c.w.name} scale {scale:g} big {big}: {err:.2e}")
+    assert err <= 2.0 ** -20 * 4
