@@ -7,14 +7,26 @@
 //
 // Two launches per call, both latency-bound at batch 1:
 //   scan    one workgroup per (row, 2048-logit chunk): the chunk's max m and
-//           its sums of e^(z-m), (m-z) e^(z-m) and e^(2(z-m)), and the chunk's
-//           own top-K (a chunk's K largest contain every global winner that
-//           falls in it) by radix selection over unique 64-bit keys;
+//           its sums of e^(z-m), (m-z) e^(z-m) and e^(2(z-m)), and the largest
+//           key of each of its G groups of 2048 / G neighbouring logits (G the
+//           largest power of two up to K);
 //   finish  one workgroup per row: the log-sum-exp and entropy from the
-//           chunk sums, the global top-K from the chunks' candidates (again
-//           by radix selection), its order by rank counting, the 12
+//           chunk sums, the global top-K, its order by rank counting, the 12
 //           features, the detector and, when r > tau, the corrector over the
 //           window and the in-place merge.
+// Top-K: the K-th largest group maximum bounds the window from below, so only
+// groups whose maximum reaches it can hold a window entry.  Neighbouring
+// threads give a first bound (each set of them holds some maximum), a
+// histogram of 1024 bins over the maxima above it the bin of the K-th, and the
+// logits of the K and a few groups from that bin up are read again, filtered
+// and ranked by counting.  Where that resolves too little (ties, an outlier
+// far above the rest, NaN or +inf among the maxima) a radix selection over the
+// keys takes its place.  V = 128256, K = 128, one row: scan 3.7 and finish
+// 11.0 us; with a radix selection of every chunk's own top-K in the scan and
+// another of the 8064 survivors in the finish 9.1 and 13.8.  Of the finish's
+// 25 thousand cycles 6 are the first loads, 5 the selection, 5 the second read
+// of the logits, 3 the ranks and 6 the features and the two MLPs, one after
+// the other on one compute unit.
 //
 // Keys: the high 32 bits order the fp32 logits (sign-flipped bit patterns),
 // the low 32 bits hold ~index, so that among equal logits the lower index
@@ -183,99 +195,119 @@ __device__ uint64_t select_threshold(const uint64_t (&key)[IPT], int want, uint3
   }
 }
 
-// Block sums of three values over kScanThreads threads (four waves).
-__device__ __forceinline__ void block_sum4x3(float& a, float& b, float& c, float* red) {
-  a = wave_sum(a);
-  b = wave_sum(b);
-  c = wave_sum(c);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    red[w] = a;
-    red[4 + w] = b;
-    red[8 + w] = c;
-  }
-  __syncthreads();
-  a = (red[0] + red[1]) + (red[2] + red[3]);
-  b = (red[4] + red[5]) + (red[6] + red[7]);
-  c = (red[8] + red[9]) + (red[10] + red[11]);
-  __syncthreads();
+// Logit groups per chunk: the largest power of two up to k (at most 256).
+__host__ __device__ inline int chunk_groups(int k) {
+  int g = 8;
+  while (2 * g <= k && g < kScanThreads) g *= 2;
+  return g;
 }
-__device__ __forceinline__ float block_max4(float v, float* red) {
-  v = wave_max(v);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) red[w] = v;
-  __syncthreads();
-  const float m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  return m;
+
+__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
+  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, mask), hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), mask);
+  return ((uint64_t)hi << 32) | lo;
 }
 
 __global__ __launch_bounds__(kScanThreads) void dgap_scan_kernel(DgapArgs a) {
-  __shared__ uint32_t hist[256], sel[4], ext[4 * kScanThreads / 64];
-  __shared__ float red[12];
-  const int row = blockIdx.x / a.nchunk, chunk = blockIdx.x % a.nchunk;
+  __shared__ float4 part[kScanThreads / 64];
+  __shared__ float wmax[kScanThreads / 64];
+  static_assert(kScanThreads == 256, "four waves");
+  typedef float f4_t __attribute__((ext_vector_type(4)));
+  typedef f4_t f4_any __attribute__((aligned(4)));
+  const int row = blockIdx.x / a.nchunk, chunk = blockIdx.x % a.nchunk, tid = threadIdx.x;
   const float* z = a.logits + (size_t)row * a.vocab;
-  const int base = chunk * kDgapChunk;
+  const int i0 = chunk * kDgapChunk + tid * kScanItems, n = min(kScanItems, a.vocab - i0);  // this thread's logits
+  static_assert(kScanItems == 8, "two 16-byte loads per thread");
   float v[kScanItems];
-  uint64_t key[kScanItems];
-  float m = -__builtin_inff();
+  if (n == kScanItems) {
+    const f4_t x = *reinterpret_cast<const f4_any*>(z + i0), y = *reinterpret_cast<const f4_any*>(z + i0 + 4);
 #pragma unroll
-  for (int j = 0; j < kScanItems; ++j) {
-    const int i = base + j * kScanThreads + threadIdx.x;
-    const bool in = i < a.vocab;
-    v[j] = in ? z[i] : -__builtin_inff();
-    key[j] = in ? make_key(v[j], (uint32_t)i) : 0;
+    for (int j = 0; j < 4; ++j) {
+      v[j] = x[j];
+      v[4 + j] = y[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kScanItems; ++j) v[j] = j < n ? z[i0 + j] : -__builtin_inff();
+  }
+  float m = v[0];
+  uint32_t top = order_bits(v[0]);
+  int at = 0;  // the first of the largest
+#pragma unroll
+  for (int j = 1; j < kScanItems; ++j) {
+    const uint32_t o = j < n ? order_bits(v[j]) : 0u;
+    at = o > top ? j : at;
+    top = max(top, o);
     m = fmaxf(m, v[j]);
   }
-  m = block_max4(m, red);
+  // the largest key of each group: one lane, or up to 32 neighbours
+  uint64_t key = n > 0 ? ((uint64_t)top << 32) | (uint64_t)(~(uint32_t)(i0 + at)) : 0;
+  const int G = chunk_groups(a.k), tpg = kScanThreads / G;
+  for (int d = 1; d < tpg; d *= 2) {
+    const uint64_t o = shfl_xor_u64(key, d);
+    key = o > key ? o : key;
+  }
+  if (tid % tpg == 0) a.ws_cand[((size_t)row * a.nchunk + chunk) * a.k + tid / tpg] = key;
+  m = wave_max(m);
+  if ((tid & 63) == 0) wmax[tid >> 6] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
   float s = 0.f, t = 0.f, u = 0.f;
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
-    if (key[j] != 0) {
+    if (j < n) {
       const float e = expf(v[j] - m);
       s += e;
       t = fmaf(e, m - v[j], t);  // >= 0 term by term: the entropy needs no cancellation
       u = fmaf(e, e, u);
     }
   }
-  block_sum4x3(s, t, u, red);
-  float* st = a.ws_stats + ((size_t)row * a.nchunk + chunk) * 4;
-  if (threadIdx.x == 0) {
-    st[0] = m;
-    st[1] = s;
-    st[2] = t;
-    st[3] = u;
-  }
-  // the chunk's top-K (all of it when the chunk is shorter)
-  const int n = min(kDgapChunk, a.vocab - base);
-  const int want = min(a.k, n);
-  uint64_t* out = a.ws_cand + ((size_t)row * a.nchunk + chunk) * a.k;
-  const uint64_t T = want < n ? select_threshold<kScanThreads, kScanItems>(key, want, hist, sel, ext) : 1;
-  if (threadIdx.x == 0) sel[3] = 0;
+  s = wave_sum(s);
+  t = wave_sum(t);
+  u = wave_sum(u);
+  if ((tid & 63) == 0) part[tid >> 6] = make_float4(m, s, t, u);
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kScanItems; ++j)
-    if (key[j] != 0 && key[j] >= T) {
-      const uint32_t slot = atomicAdd(&sel[3], 1u);
-      if (slot < (uint32_t)want) out[slot] = key[j];  // exactly `want` keys pass
-    }
-  for (int i = want + threadIdx.x; i < a.k; i += kScanThreads) out[i] = 0;  // empty slots
+  if (tid < 4) {  // lane 0: m, 1: s, 2: t, 3: u
+    const float* p = &part[0].x + tid;
+    const float sum = (p[0] + p[4]) + (p[8] + p[12]);
+    a.ws_stats[((size_t)row * a.nchunk + chunk) * 4 + tid] = tid == 0 ? m : sum;
+  }
 }
 
-// IPT: candidate keys per thread (the launch picks the smallest of 8, 16, 32
-// that holds chunks * K).
+constexpr int kBins = 1024;
+constexpr int kListMax = 2048;   // groups that are binned
+constexpr int kRegather = 8;     // logits of the selected groups a finish thread holds at most
+constexpr int kRankMax = 1024;   // candidates that rank counting takes
+constexpr int kRankPad = 64;     // zeros past them: a thread reads 16 keys, every fourth pair, at a time
+
+// This thread's first slot of `own` in a list that the block fills: one LDS
+// atomic per wave (of its own accord the compiler adds lane by lane).
+__device__ __forceinline__ uint32_t wave_slots(uint32_t own, uint32_t* count) {
+  const uint32_t sum = wave_prefix_sum(own);
+  uint32_t base = 0;
+  if ((threadIdx.x & 63) == 63 && sum != 0) base = atomicAdd(count, sum);
+  return (uint32_t)__builtin_amdgcn_readlane((int)base, 63) + sum - own;
+}
+
+// IPT: group maxima per thread (the launch picks the smallest of 8, 16, 32
+// that holds them).
 template <int IPT>
 __global__ __launch_bounds__(kFinishThreads) void dgap_finish_kernel(DgapArgs a) {
-  constexpr int kW1 = kDgapFeatures * kDgapMaxHidden, kC1 = (kDgapCandInputs + kDgapFeatures) * kDgapMaxHidden;
-  __shared__ float wdet[kW1 + 2 * kDgapMaxHidden], wcor[kC1 + 2 * kDgapMaxHidden];
-  __shared__ uint32_t hist[256], sel[4], ext[4 * kFinishThreads / 64];
-  __shared__ uint64_t win[kDgapMaxK], skey[kDgapMaxK];
+  // one row of 64 hidden units (zeros past the last) per input, then the bias and the output weights
+  constexpr int kWaves = kFinishThreads / 64, kDet = kDgapFeatures + 2, kCorrIn = kDgapCandInputs + kDgapFeatures;
+  static_assert(kDgapMaxHidden == 64, "a weight row per wave");
+  __shared__ __attribute__((aligned(16))) float wdet[kDet][64], wcor[kCorrIn + 2][64];
+  __shared__ __attribute__((aligned(16))) uint32_t bins[kBins];
+  __shared__ __attribute__((aligned(16))) uint32_t ext[4 * kWaves];
+  __shared__ uint32_t hist[256], sel[4], cnt[4];
+  __shared__ uint2 list[kListMax];  // (order of the maximum, group)
+  __shared__ uint16_t groups[kRegather * kFinishThreads / 8];  // selected groups (8 logits at least each)
+  __shared__ __attribute__((aligned(16))) uint64_t win[kRankMax + kRankPad], skey[kDgapMaxK];
   __shared__ float stat[8];      // lse, H, sum p^2, r
   __shared__ float phi[kDgapFeatures];
   __shared__ float vsorted[kDgapMaxK];
-  __shared__ float uphi[kDgapMaxHidden];
+  __shared__ __attribute__((aligned(16))) float uphi[kDgapMaxHidden];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int K = a.k, ncand = a.nchunk * K;
+  const int K = a.k, G = chunk_groups(K), gshift = __builtin_ctz(G), ngroup = a.nchunk * G;
   float* z = a.logits + (size_t)row * a.vocab;
   const int hd = a.hidden_det, hc = a.hidden_corr;
 
@@ -284,31 +316,36 @@ __global__ __launch_bounds__(kFinishThreads) void dgap_finish_kernel(DgapArgs a)
   // concatenation det_w1, det_b1, det_w2, corr_w1, corr_b1, corr_w2) and,
   // in wave 0, the statistics of the first 64 chunks.
   uint64_t key[IPT];
-  const uint64_t* cand = a.ws_cand + (size_t)row * ncand;
+  const uint64_t* cand = a.ws_cand + (size_t)row * a.nchunk * K;
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
     const int i = j * kFinishThreads + tid;
-    key[j] = i < ncand ? cand[i] : 0;
+    key[j] = i < ngroup ? cand[(size_t)(i >> gshift) * K + (i & (G - 1))] : 0;
   }
-  const int seg[6] = {kDgapFeatures * hd, hd, hd, (kDgapCandInputs + kDgapFeatures) * hc, hc, hc};
-  const float* src[6] = {a.det_w1, a.det_b1, a.det_w2, a.corr_w1, a.corr_b1, a.corr_w2};
-  float* dst[6] = {wdet, wdet + kW1, wdet + kW1 + kDgapMaxHidden, wcor, wcor + kC1, wcor + kC1 + kDgapMaxHidden};
-  float wv3[3];
-  int ws3[3], wo3[3];
+  constexpr int kRows = kDet + kCorrIn + 2, kRowsPerWave = (kRows + kWaves - 1) / kWaves;
+  float wrow[kRowsPerWave];
 #pragma unroll
-  for (int r3 = 0; r3 < 3; ++r3) {
-    int i = tid + r3 * kFinishThreads, sgi = 0;
-    while (sgi < 6 && i >= seg[sgi]) i -= seg[sgi++];
-    ws3[r3] = sgi;
-    wo3[r3] = i;
-    wv3[r3] = sgi < 6 ? src[sgi][i] : 0.f;
+  for (int i = 0; i < kRowsPerWave; ++i) {
+    const int r = wv + i * kWaves, c = r - kDet;  // c: row of the corrector
+    const float* src = r < kDgapFeatures       ? a.det_w1 + r * hd
+                       : r == kDgapFeatures    ? a.det_b1
+                       : r < kDet              ? a.det_w2
+                       : c < kCorrIn           ? a.corr_w1 + c * hc
+                       : c == kCorrIn          ? a.corr_b1
+                                               : a.corr_w2;
+    wrow[i] = r < kRows && lane < (r < kDet ? hd : hc) ? src[lane] : 0.f;
   }
   const float* st = a.ws_stats + (size_t)row * a.nchunk * 4;
   float4 st0 = make_float4(-__builtin_inff(), 0.f, 0.f, 0.f);
   if (wv == 0 && lane < a.nchunk) st0 = *reinterpret_cast<const float4*>(st + 4 * lane);
 #pragma unroll
-  for (int r3 = 0; r3 < 3; ++r3)
-    if (ws3[r3] < 6) dst[ws3[r3]][wo3[r3]] = wv3[r3];
+  for (int i = 0; i < kRowsPerWave; ++i) {
+    const int r = wv + i * kWaves;
+    if (r < kDet)
+      wdet[r][lane] = wrow[i];
+    else if (r < kRows)
+      wcor[r - kDet][lane] = wrow[i];
+  }
 
   // log-sum-exp, entropy and concentration from the chunk sums (wave 0)
   if (wv == 0) {
@@ -338,37 +375,190 @@ __global__ __launch_bounds__(kFinishThreads) void dgap_finish_kernel(DgapArgs a)
     }
   }
 
-  // the global window: the K largest candidate keys, then their order
-  const uint64_t T = select_threshold<kFinishThreads, IPT>(key, K, hist, sel, ext);
-  if (tid == 0) sel[3] = 0;
+  // The groups that can hold a window entry.  First a value that at least K maxima reach: 16,
+  // 8 or 4 neighbouring threads hold some maximum, and there are 64, 128 or 256 such sets.
+  // (Where a set holds none, the smallest maximum.)
+  static_assert(kBins == kFinishThreads && kRankMax == kFinishThreads, "one entry per thread to clear");
+  static_assert(kFinishThreads / 4 >= kDgapMaxK, "a quad per window entry");
+  bins[tid] = 0;
+  win[tid] = 0;
+  if (tid < kRankPad) win[kRankMax + tid] = 0;
+  if (tid < 4) cnt[tid] = 0;
+  uint32_t top = 0, bottom = ~0u;
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) {
+    const uint32_t o = (uint32_t)(key[j] >> 32);
+    top = max(top, o);
+    bottom = min(bottom, key[j] != 0 ? o : ~0u);
+  }
+  uint32_t set = max(top, dpp_u32<kQuadXor1>(0u, top));
+  set = max(set, dpp_u32<kQuadXor2>(0u, set));
+  if (K <= kFinishThreads / 8) set = max(set, dpp_u32<kHalfMirror>(0u, set));
+  if (K <= kFinishThreads / 16) set = max(set, dpp_u32<kMirror>(0u, set));
+  set = wave_min_u32(set);
+  top = wave_max_u32(top);
+  bottom = wave_min_u32(bottom);
+  if (lane == 0) *reinterpret_cast<uint4*>(&ext[4 * wv]) = make_uint4(set, top, bottom, 0u);
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < IPT; ++j)
-    if (key[j] != 0 && key[j] >= T) {
-      const uint32_t slot = atomicAdd(&sel[3], 1u);
-      if (slot < (uint32_t)K) win[slot] = key[j];  // exactly K keys pass
+  for (int w = 0; w < kWaves; ++w) {
+    const uint4 x = *reinterpret_cast<const uint4*>(&ext[4 * w]);
+    set = min(set, x.x);
+    top = max(top, x.y);
+    bottom = min(bottom, x.z);
+  }
+  const uint32_t lo_bits = max(set, bottom);
+  const int E = kDgapChunk >> gshift, eshift = __builtin_ctz(E);  // logits per group
+  const int most = kRegather * kFinishThreads >> eshift;          // groups that can be read again
+  // NaN and +inf have no bins, and fewer than K maxima say nothing of the rest
+  bool binned = top < order_bits(__builtin_inff()) && bottom >= order_bits(-__builtin_inff());
+  const float lo = from_order_bits(lo_bits), scale = (float)kBins / (from_order_bits(top) - lo);
+  // monotone; NaN products (an infinite scale or distance) go to bin 0
+  auto bin_of = [&](float v) -> int { return (int)fminf(fmaxf((v - lo) * scale, 0.f), (float)(kBins - 1)); };
+  int thr = 0, id = tid;  // a group's number is id + 1024 j: computed anew, or the loads' 32 indices stay in registers
+  asm volatile("" : "+v"(id));
+  if (binned) {
+    uint32_t own = 0;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) own += (uint32_t)(key[j] >> 32) >= lo_bits;  // (-inf is above an empty slot)
+    uint32_t slot = wave_slots(own, &cnt[3]);
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const uint32_t o = (uint32_t)(key[j] >> 32);
+      if (o >= lo_bits && slot < (uint32_t)kListMax) list[slot++] = make_uint2(o, j * kFinishThreads + id);
     }
-  __syncthreads();
+    __syncthreads();
+    const int n = (int)cnt[3];
+    binned = n >= K && n <= kListMax;
+    if (binned) {
+      int bin[kListMax / kFinishThreads];
+      uint16_t group[kListMax / kFinishThreads];
+#pragma unroll
+      for (int i = 0; i < kListMax / kFinishThreads; ++i) {
+        bin[i] = -1;
+        if (i * kFinishThreads + tid >= n) continue;
+        const uint2 x = list[i * kFinishThreads + tid];
+        group[i] = (uint16_t)x.y;
+        bin[i] = bin_of(from_order_bits(x.x));
+        atomicAdd(&bins[bin[i]], 1u);
+      }
+      __syncthreads();
+      if (wv == 0) {  // lane l holds bins kBins - 1 - 16 l and the 15 below it
+        static_assert(kBins == 16 * 64, "16 bins per lane");
+        uint32_t c[16], own = 0;
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+          const uint4 x = *reinterpret_cast<const uint4*>(&bins[kBins - 4 - 16 * lane - i]);
+          c[i] = x.w;
+          c[i + 1] = x.z;
+          c[i + 2] = x.y;
+          c[i + 3] = x.x;
+          own += (x.x + x.y) + (x.z + x.w);
+        }
+        uint32_t before = wave_prefix_sum(own) - own;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          if (before < (uint32_t)K && before + c[i] >= (uint32_t)K) sel[0] = kBins - 1 - 16 * lane - i;
+          before += c[i];
+        }
+      }
+      __syncthreads();
+      thr = (int)sel[0];
+#pragma unroll
+      for (int i = 0; i < kListMax / kFinishThreads; ++i)
+        if (bin[i] >= thr) {
+          const uint32_t slot = atomicAdd(&cnt[0], 1u);
+          if (slot < (uint32_t)most) groups[slot] = group[i];
+        }
+      __syncthreads();
+    }
+  }
+  if (!binned) {  // every group
+    uint32_t own = 0;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) own += key[j] != 0;
+    uint32_t slot = wave_slots(own, &cnt[0]);
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      if (key[j] != 0 && slot < (uint32_t)most) groups[slot++] = (uint16_t)(j * kFinishThreads + id);
+    }
+    __syncthreads();
+  }
+  uint64_t floor_key = 0;  // a lower bound on the window's keys, where the bins resolve too little
+  if (cnt[0] > (uint32_t)most) {
+    floor_key = select_threshold<kFinishThreads, IPT>(key, K, hist, sel, ext);
+    if (tid == 0) cnt[0] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < IPT; ++j)
+      if (key[j] >= floor_key && key[j] != 0) groups[atomicAdd(&cnt[0], 1u)] = (uint16_t)(j * kFinishThreads + id);  // K of them
+    __syncthreads();
+  }
+  // their logits again: at most kRegather per thread
+  const int nsel = (int)cnt[0], nread = nsel << eshift;
+  uint64_t again[kRegather];  // as read: value, ~index
+#pragma unroll
+  for (int j = 0; j < kRegather; ++j) {
+    again[j] = 0;
+    if (j * kFinishThreads >= nread) continue;
+    const int i = j * kFinishThreads + tid;
+    const int at = i < nread ? (groups[i >> eshift] << eshift) + (i & (E - 1)) : a.vocab;  // chunk * 2048 + group * E + element
+    if (at < a.vocab) again[j] = ((uint64_t)__builtin_bit_cast(uint32_t, z[at]) << 32) | (uint64_t)(~(uint32_t)at);
+  }
+  uint32_t mine = 0;
+#pragma unroll
+  for (int j = 0; j < kRegather; ++j) {
+    if (j * kFinishThreads >= nread || again[j] == 0) continue;
+    const float v = __builtin_bit_cast(float, (uint32_t)(again[j] >> 32));
+    const uint64_t k = make_key(v, key_index(again[j]));
+    again[j] = (floor_key != 0 ? k >= floor_key : !binned || (v >= lo && bin_of(v) >= thr)) ? k : 0;
+    mine += again[j] != 0;
+  }
   {
-    // rank of window entry c = #{larger entries}: four threads per entry
-    const int c = tid >> 2, part = tid & 3;
-    const uint64_t mine = c < K ? win[c] : 0;
+    uint32_t slot = wave_slots(mine, &cnt[1]);
+#pragma unroll
+    for (int j = 0; j < kRegather; ++j)
+      if (again[j] != 0) {
+        if (slot < (uint32_t)kRankMax) win[slot] = again[j];
+        ++slot;
+      }
+  }
+  __syncthreads();
+  int nwin = (int)cnt[1];
+  if (nwin > kRankMax) {  // too many for rank counting: exactly the K largest
+    const uint64_t T = select_threshold<kFinishThreads, kRegather>(again, K, hist, sel, ext);
+    win[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kRegather; ++j)
+      if (again[j] != 0 && again[j] >= T) {
+        const uint32_t slot = atomicAdd(&cnt[2], 1u);
+        if (slot < (uint32_t)K) win[slot] = again[j];  // exactly K keys pass
+      }
+    nwin = K;
+    __syncthreads();
+  }
+  {
+    // rank of candidate c = #{larger ones}: four, two or one threads each
+    const int pshift = nwin <= kFinishThreads / 4 ? 2 : nwin <= kFinishThreads / 2 ? 1 : 0, parts = 1 << pshift;
+    const int c = tid >> pshift, part = tid & (parts - 1);
+    const uint64_t mine_key = c < nwin ? win[c] : 0;
     int rank = 0;
-    if (c < K) {
-      for (int j0 = part; j0 < K; j0 += 4 * 16) {  // 16 reads in flight
-        uint64_t o[16];
+    if (c < nwin) {
+      for (int j0 = 2 * part; j0 < nwin; j0 += 16 * parts) {
+        ulonglong2 o[8];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) o[u] = j0 + 4 * u < K ? win[j0 + 4 * u] : 0;
+        for (int u = 0; u < 8; ++u) o[u] = *reinterpret_cast<const ulonglong2*>(&win[j0 + 2 * u * parts]);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) rank += o[u] > mine;
+        for (int u = 0; u < 8; ++u) rank += (o[u].x > mine_key) + (o[u].y > mine_key);
       }
     }
-    // the four threads of an entry are one lane quad
-    rank += (int)dpp_u32<kQuadXor1>(0u, (uint32_t)rank);
-    rank += (int)dpp_u32<kQuadXor2>(0u, (uint32_t)rank);
-    if (c < K && part == 0) {
-      skey[rank] = mine;
-      vsorted[rank] = key_value(mine);
+    // the threads of a candidate are neighbouring lanes
+    if (pshift >= 1) rank += (int)dpp_u32<kQuadXor1>(0u, (uint32_t)rank);
+    if (pshift >= 2) rank += (int)dpp_u32<kQuadXor2>(0u, (uint32_t)rank);
+    if (c < nwin && part == 0 && rank < K) {
+      skey[rank] = mine_key;
+      vsorted[rank] = key_value(mine_key);
     }
   }
   __syncthreads();
@@ -422,17 +612,20 @@ __global__ __launch_bounds__(kFinishThreads) void dgap_finish_kernel(DgapArgs a)
   }
   __syncthreads();
 
-  // detector: lane h is hidden unit h (wave 0)
+  // detector: lane h is hidden unit h (wave 0); the phi part of the corrector's
+  // hidden units, the same for every candidate (wave 1)
   if (wv == 0) {
-    float y = 0.f;
-    if (lane < hd) {
-      float acc = wdet[kW1 + lane];
+    float acc = wdet[kDgapFeatures][lane];
 #pragma unroll
-      for (int i = 0; i < kDgapFeatures; ++i) acc = fmaf(phi[i], wdet[i * hd + lane], acc);
-      y = fmaxf(acc, 0.f) * wdet[kW1 + kDgapMaxHidden + lane];
-    }
+    for (int i = 0; i < kDgapFeatures; ++i) acc = fmaf(phi[i], wdet[i][lane], acc);
+    const float y = lane < hd ? fmaxf(acc, 0.f) * wdet[kDgapFeatures + 1][lane] : 0.f;
     const float s = wave_sum(y) + a.det_b2;
     if (lane == 0) stat[3] = 1.f / (1.f + expf(-s));
+  } else if (wv == 1) {
+    float uh = wcor[kCorrIn][lane];
+#pragma unroll
+    for (int i = 0; i < kDgapFeatures; ++i) uh = fmaf(phi[i], wcor[kDgapCandInputs + i][lane], uh);
+    uphi[lane] = uh;
   }
   __syncthreads();
   const float r = stat[3];
@@ -440,27 +633,31 @@ __global__ __launch_bounds__(kFinishThreads) void dgap_finish_kernel(DgapArgs a)
   float* info = a.info ? a.info + (size_t)row * (kDgapInfoHead + 2 * K) : nullptr;
 
   if (correct) {
-    // corrector: the phi part of hidden unit h's input is the same for every
-    // candidate (wave 0 computes it); then four threads (a lane quad) per
-    // candidate, 16 hidden units each
-    if (wv == 0 && lane < hc) {
-      float uh = wcor[kC1 + lane];
-#pragma unroll
-      for (int i = 0; i < kDgapFeatures; ++i) uh = fmaf(phi[i], wcor[(kDgapCandInputs + i) * hc + lane], uh);
-      uphi[lane] = uh;
-    }
-    __syncthreads();
+    // corrector: four threads (a lane quad) per candidate, 16 hidden units
+    // each (those past the last are left out: 0 times an infinite input)
     const int k = tid >> 2, g = tid & 3;
     float part = 0.f, vk = 0.f;
     if (k < K) {
       vk = vsorted[k];
       const float xi[kDgapCandInputs] = {vk - vsorted[0], vk - lse, (float)k / (float)(K - 1),
                                          k > 0 ? vsorted[k - 1] - vk : 0.f, k + 1 < K ? vk - vsorted[k + 1] : 0.f};
-      for (int h = 16 * g; h < min(hc, 16 * g + 16); ++h) {
-        float acc = uphi[h];
 #pragma unroll
-        for (int i = 0; i < kDgapCandInputs; ++i) acc = fmaf(xi[i], wcor[i * hc + h], acc);
-        part = fmaf(fmaxf(acc, 0.f), wcor[kC1 + kDgapMaxHidden + h], part);
+      for (int u = 0; u < 16; u += 4) {  // the quad reads 64 bytes side by side
+        const int h0 = 4 * u + 4 * g;
+        float acc[4];
+        *reinterpret_cast<float4*>(acc) = *reinterpret_cast<const float4*>(&uphi[h0]);
+#pragma unroll
+        for (int i = 0; i < kDgapCandInputs; ++i) {
+          float w[4];
+          *reinterpret_cast<float4*>(w) = *reinterpret_cast<const float4*>(&wcor[i][h0]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = fmaf(xi[i], w[e], acc[e]);
+        }
+        float w2[4];
+        *reinterpret_cast<float4*>(w2) = *reinterpret_cast<const float4*>(&wcor[kCorrIn + 1][h0]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (h0 + e < hc) part = fmaf(fmaxf(acc[e], 0.f), w2[e], part);
       }
     }
     part += __builtin_bit_cast(float, dpp_u32<kQuadXor1>(0u, __builtin_bit_cast(uint32_t, part)));
@@ -493,7 +690,7 @@ int launch_dgap(const DgapArgs& a, int batch, void* stream) {
   hipLaunchKernelGGL(dgap_scan_kernel, dim3(batch * a.nchunk), dim3(kScanThreads), 0, (hipStream_t)stream, a);
   int e = (int)hipGetLastError();
   if (e) return e;
-  const int ncand = a.nchunk * a.k;
+  const int ncand = a.nchunk * chunk_groups(a.k);
   if (ncand <= 8 * kFinishThreads)
     hipLaunchKernelGGL(dgap_finish_kernel<8>, dim3(batch), dim3(kFinishThreads), 0, (hipStream_t)stream, a);
   else if (ncand <= 16 * kFinishThreads)
