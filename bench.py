@@ -346,9 +346,11 @@ def dgap_leg(workload_idx: int, bits: int, iters: int):
         b.record()
         torch.cuda.synchronize()
         out[f"us_{name}"] = round(a.elapsed_time(b) * 1e3 / iters, 3)
-    # bytes one call must move: the row (read once) and the chunk partials
+    # bytes one call must move: the row (read once), the chunk sums and the
+    # group maxima (the largest power of two up to k per chunk)
     nchunk = -(-V // 2048)
-    out["bytes_per_call"] = V * 4 + nchunk * (16 + 8 * k) * 2 + 2 * k * 4
+    groups = 1 << (k.bit_length() - 1)
+    out["bytes_per_call"] = V * 4 + nchunk * (16 + 8 * groups) * 2 + 2 * k * 4
     out["gbs_corrected"] = round(out["bytes_per_call"] / (out["us_corrected"] * 1e-6) / 1e9, 2)
     out["bound"] = "latency (two dependent launches; the row is 0.5-0.6 MB)"
     return out
@@ -359,10 +361,14 @@ CHUNK_SIZES = (4, 5, 16, 64)
 
 def chunk_row_groups(n_q: int, gq: int):
     """Rows per group and groups per kv head as the library plans chunk
-    queries on 1- and 2-bit caches with value groups of 32: of 32 or 16 rows
-    (the chunk kernel, floor(rows / gq) queries each) and 8, 5 or 4 (the
-    decode kernel, whole sets of heads), the one with the fewest estimated
-    microseconds, ceil(n_q / queries) passes at 38, 30, 21, 19 or 18."""
+    queries on 1- and 2-bit caches with value groups of 32: 80 rows or more
+    take the many-row kernel (256 rows, floor(32 / gq) queries in each of its
+    eight waves); fewer take groups of 32 or 16 rows (the chunk kernel,
+    floor(rows / gq) queries each) or 8, 5 or 4 (the decode kernel, whole sets
+    of heads), the one with the fewest estimated microseconds,
+    ceil(n_q / queries) passes at 38, 30, 21, 19 or 18."""
+    if n_q * gq >= 80:
+        return 256, -(-n_q // (8 * (32 // gq)))
     cost = {32: 38, 16: 30, 8: 21, 5: 19, 4: 18}
     best = None
     for r in (32, 16, 8, 5, 4):
@@ -413,8 +419,8 @@ def chunk_leg(handles, w, launch_bytes: int, stream, iters: int):
         out["row_groups_per_kv_head"].append(groups)
         out["rows_per_group"].append(rows)
         del q, o, ws
-    out["note"] = ("each row group of up to 32 (query, head) rows is one pass over the kv head's cache "
-                   "(the chunk kernel: two row halves of 16 share each unpacked code operand); a last group "
+    out["note"] = ("each row group of up to 32 (query, head) rows, or 256 in the many-row kernel, is one pass over "
+                   "the kv head's cache (two row halves of 16 share each unpacked code operand); a last group "
                    "with fewer queries repeats the last one in its spare rows (n_q = 5: one 32-row group, the "
                    "verification step of 4 drafted tokens); the useful flops count each visible (query, head, "
                    "token) once")

@@ -220,7 +220,8 @@ size_t kvq_chunk_workspace_bytes(const kvq_cache* cache, int32_t n_q);
  * 16-byte aligned, contents undefined on entry and exit.  Every sequence
  * must hold at least n_q tokens.  With n_q = 1 the result equals
  * kvq_decode_attention's.  The queries of a kv head are read in groups of
- * up to 8 (query, head) rows, each group one pass over the cache.
+ * up to 32 (query, head) rows, or of 256 where there are many, each group
+ * one pass over the cache.
  * Errors: KVQ_ERR_ARG (n_q out of range, a sequence shorter than n_q, null
  * pointers, misaligned workspace), KVQ_ERR_CAPACITY (workspace too small),
  * KVQ_ERR_HIP. */
