@@ -825,7 +825,7 @@ def main():
                        "*_median: median of per-launch event pairs"),
             "traffic": traffic,
             "kernel": (f"decode_mfma_kernel<{w.bits_k[0]},{w.bits_v[0]},{w.key_group // 32},{w.group_q},false,false>" if matrix_path(w) else
-                       f"decode_split_kernel<{w.bits_k[0]},{w.bits_v[0]},{w.group_q}>"),
+                       f"decode_exact_kernel<{w.bits_k[0]},{w.bits_v[0]},{str(w.value_group < 32).lower()}>"),
             "bytes_per_launch": launch_bytes,
             "kernel_source_sha256_16": source_digest(),
         },

@@ -2,7 +2,7 @@
 // or 4- or 8-bit keys and values, and 1, 2, 4, 5 or 8 query heads per kv head
 // (gfx950, v_mfma_f32_16x16x32_f16).
 //
-// Same result as the vector kernel: softmax(q K^T / sqrt(d)) V over the
+// Result: softmax(q K^T / sqrt(d)) V over the
 // dequantized cache (Introduction: scaled dot-product attention), split-K
 // over tokens with an online softmax in base 2.  At one or two bits a token
 // of one kv head carries 64-96 bytes but 2 * 4 * 128 multiply-adds, more than
