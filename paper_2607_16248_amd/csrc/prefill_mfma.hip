@@ -13,8 +13,8 @@
 // four and eight bits, whose products take two fp16 parts, hi = fl(x) and
 // lo = x - hi.  One bit has K' = s (1 - 2 code), the scale with the code as
 // its sign bit: score = sum_c q (z + s/2) - 1/2 sum_c q K'.  q enters as the
-// fp16 it is, p as fp16 (weights up to 2^14) for the value product and as
-// hi + lo for the zero-point terms and the denominator.
+// fp16 it is, p as fp16 (weights up to 2^14) for the packed values' product and
+// as hi + lo for the zero-point terms, the denominator and the fp16 tail.
 //
 // Both products are transposed, so that the first one's output is the second
 // one's operand without a lane exchange:
@@ -393,6 +393,28 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
   };
 
+  // fp16 tail: both halves of the weights meet the raw values (the product the
+  // other chunk kernels' tails make, tail_mfma.h).  A tail is a window and a key
+  // group long, so its blocks are few.
+  auto tail_values = [&](int b) {
+    const u4_t(*op)[64] = sm.op[b & (kSlots - 1)];
+    const h8_t ones = __builtin_bit_cast(h8_t, op[kZOp][lane]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      zac[u] = mfma(ones, ph[u], zac[u]);
+      zac[u] = mfma(ones, pl[u], zac[u]);
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const h8_t v = __builtin_bit_cast(h8_t, op[8 * PK + t * PV][lane]);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        acc[u][t] = mfma(v, ph[u], acc[u][t]);
+        acc[u][t] = mfma(v, pl[u], acc[u][t]);
+      }
+    }
+  };
+
   // the constant part of the operand [z; s; 1]
   for (int i = threadIdx.x; i < kSlots * 64; i += 64 * kNW) {
     const uint32_t w = (i & 15) == 8 ? 0x3C003C00u : 0u;
@@ -486,8 +508,8 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
       if (32 * b < wave_limit) {
         f4_t d[2][2];
         scores(b, d);
-        softmax(yes, no, b, d, [&] { fetch(b); });
-        values(b);
+        softmax(yes, no, b, d, [] {});
+        tail_values(b);
       }
     }
   }

@@ -135,3 +135,18 @@ def test_value_and_key_ranges(bits, scale):
     kvq.kvq_chunk_attention(c.cache.handle, torch.from_numpy(q).cuda(), n_q, out, ws)
     torch.cuda.synchronize()
     log(f"[prefill] worst {_check(c, q, out.cpu().numpy()):.2e}")
+
+
+# Every token fp16: keys, values and queries are exact operands and weights
+# carry hi + lo halves (2^-23), so a row is off by its scores alone, fp32 sums
+# of magnitude up to 2^5 whose absolute error is a relative one of a weight:
+# 2^-18, the bound that the tails of fewer rows hold (test_gpu_tail.py).
+@pytest.mark.parametrize("gq,bits,n_q,L", [(4, (1, 1), 20, 250), (4, (2, 2), 64, 250), (5, (2, 1), 33, 33), (8, (1, 2), 130, 130),
+                                           (4, (8, 8), 64, 300), (8, (4, 8), 40, 95)])
+def test_fp16_tokens_are_near_exact(gq, bits, n_q, L):
+    c = Case(W(f"fp16_gq{gq}_K{bits[0]}V{bits[1]}_L{L}", 2 * gq, 2, (L,), bits[0], bits[1], R=400))
+    c.append_all()
+    q, out = _run(c, n_q)
+    err = row_rel_err(out[0], oracle.chunk_seq(q[0], c.K[0], c.V[0], bits[0], bits[1], 32, 32, 400)).max()
+    log(f"[prefill] {c.w.name} n_q {n_q}: {err:.2e}")
+    assert err <= 2.0 ** -18
