@@ -122,6 +122,41 @@ __device__ __forceinline__ h8_t lifted(u4_t w, bool raw) {
   return __builtin_bit_cast(h8_t, w);
 }
 
+// The normal halves of w, and the subnormal ones lifted by 2^12 (exact): where
+// raw numbers have large and tiny ones among them, and a row may meet only the
+// tiny ones, both enter, the lifted ones times 2^-12 of the weights.
+__device__ __forceinline__ void split_subnormal(uint32_t w, uint32_t& normal, uint32_t& sub) {
+  const uint32_t mask = ((w & 0x7C00u) != 0u ? 0xFFFFu : 0u) | ((w & 0x7C000000u) != 0u ? 0xFFFF0000u : 0u);
+  const _Float16 f = (_Float16)kLift;
+  normal = w & mask;
+  sub = h2u(u2h(w & ~mask) * (h2_t){f, f});
+}
+// acc[u] += v (ph[u] + pl[u]) for raw halves v that are no longer lifted.
+template <int N>
+__device__ __forceinline__ void add_raw(u4_t w, const h8_t (&ph)[N], const h8_t (&pl)[N], f4_t (&acc)[N]) {
+  u4_t normal, sub;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    uint32_t a, b;
+    split_subnormal(w[t], a, b);
+    normal[t] = a;
+    sub[t] = b;
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    acc[u] = mfma(__builtin_bit_cast(h8_t, normal), ph[u], acc[u]);
+    acc[u] = mfma(__builtin_bit_cast(h8_t, normal), pl[u], acc[u]);
+  }
+  if (__builtin_amdgcn_ballot_w64(((sub[0] | sub[1] | sub[2] | sub[3]) & 0x7FFF7FFFu) != 0u) == 0) return;
+  const _Float16 f = (_Float16)(1.f / kLift);
+  const h8_t f8 = {f, f, f, f, f, f, f, f};
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    acc[u] = mfma(__builtin_bit_cast(h8_t, sub), ph[u] * f8, acc[u]);
+    acc[u] = mfma(__builtin_bit_cast(h8_t, sub), pl[u] * f8, acc[u]);
+  }
+}
+
 // Buffer resource over one (sequence, kv head) block.  Every load is
 // base + per-lane offset + uniform offset: the per-block part is scalar
 // arithmetic and the vector ALU does no address math.  The host keeps the

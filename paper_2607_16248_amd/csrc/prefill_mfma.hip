@@ -22,8 +22,10 @@
 //         of its row, 8 weights that are the B operand of
 //   O^T = V'^T P^T (the A operand's 8 tokens per lane are stored in that
 //         order, kvq_layout.h), with the row's softmax state in the lane.
-// A further product of P^T with [z; s; 1] gives the zero-point terms and the
-// sum of the weights.  Per 32 tokens and 16 rows: 8 + 8 + 2 MFMAs at one and
+// A further product of P^T with [z; s; 1; z'] gives the zero-point terms and the
+// sum of the weights: s lifted like the operands, and the zero-points that are
+// subnormal lifted into rows z' of their own, since products of subnormal
+// halves lose bits (mfma_common.h).  Per 32 tokens and 16 rows: 8 + 8 + 2 MFMAs at one and
 // two bits.  Key zero-point terms come from a table per wave, 16 key groups
 // at a time.
 //
@@ -60,6 +62,7 @@ constexpr int kNW = kPrefillWaves;
 constexpr int kTile = 16;           // rows of one tile (the N dimension); a wave has two
 constexpr int kSlots = 4;            // operand buffers (blocks in flight between two barriers)
 constexpr int kZGroups = 16;        // key groups per zero-point table
+constexpr int kSubRow = 12;         // first row z' of the operand [z; s; 1; z']
 constexpr int kZRow = 132;          // dwords per staged key group: s[128], z[128] (+ 4: rows start in distinct banks)
 constexpr float kTop = 14.f;        // weights stay below 2^14 ...
 constexpr float kHeadroom = 6.f;    // ... a new reference puts the largest at 2^8
@@ -71,7 +74,7 @@ typedef f4_t f4_any __attribute__((aligned(4)));
 
 template <int BK, int BV>
 struct PrefillSmem {
-  static constexpr int kOps = 8 * Code<BK>::parts + 8 * Code<BV>::parts + 1;  // K', V', [z; s; 1]
+  static constexpr int kOps = 8 * Code<BK>::parts + 8 * Code<BV>::parts + 1;  // K', V', [z; s; 1; z']
   u4_t op[kSlots][kOps][64];
   uint32_t zs[kZGroups * kZRow];
   float dz[kNW][kZGroups][32];
@@ -143,6 +146,8 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int X = value_shift<BV>(vbits);
   const h2_t vfac = operand_factor<BV>(X), kfac = operand_factor<BK>(0);
   const float unit_packed = Code<BV>::unit * ldexpf(1.f, -X);
+  const _Float16 sf = (_Float16)ldexpf(1.f, min(X + Code<BV>::reach, 13));  // scales lifted like the operands
+  const h2_t sfac = {sf, sf};
 
   // this wave's operands: keys, 16-token tile kmb and channel block kkb;
   // values, channels 16 wv .. (value group vg)
@@ -152,7 +157,7 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   const uint32_t lo_ks = (32 * kkb + 8 * blk) * 2;
   const uint32_t lo_v = lane * 8 * BV + 4 * (BV == 8 ? 2 * wv : BV == 4 ? wv : BV == 2 ? wv >> 1 : wv >> 2);
   const uint32_t lo_vs = (vg * 32 + 8 * blk) * 2;
-  // rows 0-3 (zeros) and 4-7 (scales) of the operand [z; s; 1]: 16 threads a row
+  // rows 0-3 (zeros) and 4-7 (scales) of the operand [z; s; 1; z']: 16 threads a row
   const int zrow = threadIdx.x >> 4, zpos = threadIdx.x & 15;
   const bool has_zz = zrow < 8 && (zrow & 3) < ng;
   const uint32_t lo_zz = (zrow < 4 ? fresh_vm : 0) + (zrow & 3) * 64 + zpos * 4;
@@ -204,8 +209,17 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     if constexpr (PV == 2) op[8 * PK + wv * PV + 1][lane] = lo;
   };
   auto put_zz = [&](int b, uint32_t zz) {
-    if (wv < 2 && has_zz)
-      reinterpret_cast<uint32_t*>(&sm.op[b & (kSlots - 1)][kZOp][zrow + 16 * (zpos >> 2)])[zpos & 3] = zz;
+    if (wv < 2 && has_zz) {
+      u4_t* op = &sm.op[b & (kSlots - 1)][kZOp][16 * (zpos >> 2)];
+      if (zrow < 4) {
+        uint32_t normal, sub;
+        split_subnormal(zz, normal, sub);
+        reinterpret_cast<uint32_t*>(&op[zrow])[zpos & 3] = normal;
+        reinterpret_cast<uint32_t*>(&op[kSubRow + zrow])[zpos & 3] = sub;
+      } else {
+        reinterpret_cast<uint32_t*>(&op[zrow])[zpos & 3] = h2u(u2h(zz) * sfac);
+      }
+    }
   };
   auto unpack_key = [&](int b, const Staged& o) {
     u4_t hi, lo;
@@ -394,9 +408,9 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   };
 
   // fp16 tail: both halves of the weights meet the raw values (the product the
-  // other chunk kernels' tails make, tail_mfma.h).  A tail is a window and a key
-  // group long, so its blocks are few.
-  auto tail_values = [&](int b) {
+  // other chunk kernels' tails make, tail_mfma.h), which enter lifted while they
+  // are small.  A tail is a window and a key group long, so its blocks are few.
+  auto tail_values = [&](int b, uint32_t& raw) {
     const u4_t(*op)[64] = sm.op[b & (kSlots - 1)];
     const h8_t ones = __builtin_bit_cast(h8_t, op[kZOp][lane]);
 #pragma unroll
@@ -406,16 +420,29 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      const h8_t v = __builtin_bit_cast(h8_t, op[8 * PK + t * PV][lane]);
+      const u4_t w = op[8 * PK + t * PV][lane];
+      if (!((raw >> t) & 1u) && needs_raw(w)) {
+        raw |= 1u << t;
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        acc[u][t] = mfma(v, ph[u], acc[u][t]);
-        acc[u][t] = mfma(v, pl[u], acc[u][t]);
+        for (int u = 0; u < 2; ++u) acc[u][t] *= 1.f / kLift;
       }
+      f4_t x[2] = {acc[0][t], acc[1][t]};
+      if ((raw >> t) & 1u) {
+        add_raw<2>(w, ph, pl, x);
+      } else {
+        const h8_t v = lifted(w, false);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          x[u] = mfma(v, ph[u], x[u]);
+          x[u] = mfma(v, pl[u], x[u]);
+        }
+      }
+      acc[0][t] = x[0];
+      acc[1][t] = x[1];
     }
   };
 
-  // the constant part of the operand [z; s; 1]
+  // the constant part of the operand [z; s; 1; z']
   for (int i = threadIdx.x; i < kSlots * 64; i += 64 * kNW) {
     const uint32_t w = (i & 15) == 8 ? 0x3C003C00u : 0u;
     sm.op[i >> 6][kZOp][i & 63] = (u4_t){w, w, w, w};
@@ -489,12 +516,13 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
   float unit_acc = unit_packed;  // factor of the value accumulators
   if (max(b0, nb_packed) < b1) {
-    // the tail's values carry no unit, and its rows [z; s] are zero
+    // the tail's values carry no unit but the lift, and its rows [z; s] are zero
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int t = 0; t < 8; ++t) acc[u][t] *= unit_acc;
+      for (int t = 0; t < 8; ++t) acc[u][t] *= unit_acc * kLift;
     unit_acc = 1.f;
+    uint32_t raw = 0u;  // bit t: the values of tile t enter as they are, no longer lifted
     const u4_t none = {0u, 0u, 0u, 0u};
     u4_t k, v;
     load_tail(max(b0, nb_packed), k, v);
@@ -509,9 +537,13 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
         f4_t d[2][2];
         scores(b, d);
         softmax(yes, no, b, d, [] {});
-        tail_values(b);
+        tail_values(b, raw);
       }
     }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) acc[u][t] *= (raw >> t) & 1u ? 1.f : 1.f / kLift;
   }
   if (!active) return;
 
@@ -520,7 +552,9 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   for (int u = 0; u < 2; ++u) {
     float zt[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) zt[r] = fmaf(Code<BV>::c0, __shfl(zac[u][r], 16 + col), __shfl(zac[u][r], col));
+    for (int r = 0; r < 4; ++r)
+      zt[r] = fmaf(Code<BV>::c0 / (float)sf, __shfl(zac[u][r], 16 + col),
+                   fmaf(1.f / kLift, __shfl(zac[u][r], 48 + col), __shfl(zac[u][r], col)));
     const float l = __shfl(zac[u][0], 32 + col);
     int x, head;
     row_of(kTile * u + col, x, head);

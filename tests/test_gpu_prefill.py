@@ -150,3 +150,36 @@ def test_fp16_tokens_are_near_exact(gq, bits, n_q, L):
     err = row_rel_err(out[0], oracle.chunk_seq(q[0], c.K[0], c.V[0], bits[0], bits[1], 32, 32, 400)).max()
     log(f"[prefill] {c.w.name} n_q {n_q}: {err:.2e}")
     assert err <= 2.0 ** -18
+
+
+# Subnormal values: raw ones in the tail (alone, and with one large token that
+# ends their lift), and the zero-points and scales of packed ones.  Values that
+# are constant over a token's channels are their zero-point (scale 0, codes 0),
+# which meets both halves of the weights as the tail does: the same bound.
+@pytest.mark.parametrize("gq,bits,scale,big", [(4, (1, 1), 2.0 ** -20, 0), (4, (2, 2), 2.0 ** -20, 177), (8, (8, 8), 2.0 ** -20, 90),
+                                               (5, (2, 1), 1e4, 0)])
+def test_value_ranges_of_fp16_tokens(gq, bits, scale, big):
+    c = Case(W(f"fp16_gq{gq}_K{bits[0]}V{bits[1]}_scale{scale:.0e}_big{big}", 2 * gq, 2, (200,), bits[0], bits[1], R=200))
+    c.V[0] = np.clip(c.V[0].astype(np.float32) * scale, -60000, 60000).astype(np.float16)
+    if big:
+        c.V[0][big] = (c.V[0][big].astype(np.float32) * 2.0 ** 26).astype(np.float16)
+    c.append_all()
+    q, out = _run(c, 40)
+    err = row_rel_err(out[0], oracle.chunk_seq(q[0], c.K[0], c.V[0], bits[0], bits[1], 32, 32, 200)).max()
+    log(f"[prefill] {c.w.name}: {err:.2e}")
+    # one large token can carry a row alone, with a small weight: its score's error
+    # (base 2, magnitude up to 2^6: 2^-19 of rounding per step of the sum of four
+    # products) is then the row's, not averaged over tokens
+    assert err <= (2.0 ** -17 if big else 2.0 ** -18)
+
+
+@pytest.mark.parametrize("gq,bits,gv", [(4, (1, 1), 32), (4, (2, 2), 64), (8, (8, 8), 128), (8, (4, 8), 32)])
+def test_zero_points_of_packed_tokens(gq, bits, gv):
+    c = Case(W(f"zeros_gq{gq}_K{bits[0]}V{bits[1]}_gv{gv}", 2 * gq, 2, (256,), bits[0], bits[1], gv=gv))
+    # (of one sign, so that no sum cancels)
+    c.V[0] = np.broadcast_to(np.abs(c.V[0][..., :1].astype(np.float32) * 2.0 ** -18).astype(np.float16), c.V[0].shape).copy()
+    c.append_all()
+    q, out = _run(c, 40)
+    err = row_rel_err(out[0], oracle.chunk_seq(q[0], c.K[0], c.V[0], bits[0], bits[1], 32, gv, 0)).max()
+    log(f"[prefill] {c.w.name}: {err:.2e}")
+    assert err <= 2.0 ** -18
