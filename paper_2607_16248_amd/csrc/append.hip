@@ -479,8 +479,8 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cc = lane & 15, row = lane >> 4;
   const size_t in0 = ((size_t)S.seq * a.n_max * a.hkv + h) * kHeadDim;
-  const Rows rk{a.K + in0, reinterpret_cast<const uint16_t*>(blk + a.tk), (size_t)a.hkv * kHeadDim, S.L_old, a.W, p0 >= S.L_old};
-  const Rows rv{a.V + in0, reinterpret_cast<const uint16_t*>(blk + a.tv), (size_t)a.hkv * kHeadDim, S.L_old, a.W, p0 >= S.L_old};
+  const Rows rk{a.K + in0, reinterpret_cast<const uint16_t*>(blk + region(a.tk)), (size_t)a.hkv * kHeadDim, S.L_old, a.W, p0 >= S.L_old};
+  const Rows rv{a.V + in0, reinterpret_cast<const uint16_t*>(blk + region(a.tv)), (size_t)a.hkv * kHeadDim, S.L_old, a.W, p0 >= S.L_old};
 
   u4_t kx[GK / 16];
 #pragma unroll
@@ -491,7 +491,7 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
     for (int t = 0; t < 8; ++t) vx[t] = load2<AL>(rv.at(p0 + 32 * b + value_token(wv, t)) + 2 * lane);
   };
   load_v(0);
-  uint32_t* bound = reinterpret_cast<uint32_t*>(blk + a.vb);
+  uint32_t* bound = reinterpret_cast<uint32_t*>(blk + region(a.vb));
   const uint32_t seen = __hip_atomic_load(bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // the packed segment (head region or page) of the group, and the group's
   // first token in it
@@ -556,7 +556,7 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
       case 4: par[c] = v = scale_zero<4>(a.arena, mn, mx); break;
       default: par[c] = v = scale_zero<8>(a.arena, mn, mx); break;
     }
-    uint16_t* km = reinterpret_cast<uint16_t*>(seg + a.km) + (size_t)(t0 / GK) * 2 * kHeadDim;
+    uint16_t* km = reinterpret_cast<uint16_t*>(seg + region(a.km)) + (size_t)(t0 / GK) * 2 * kHeadDim;
     km[c] = (uint16_t)v;
     km[kHeadDim + c] = (uint16_t)(v >> 16);
   }
@@ -566,8 +566,8 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
   uint32_t most = 0u;
   for (int b = 0; b < GK / 32; ++b) {
     if (b > 0) load_v(b);
-    uint8_t* vcb = seg + a.vc + (size_t)(t0 + 32 * b) * 16 * bv;
-    uint8_t* vmb = seg + a.vm + (size_t)(t0 + 32 * b) * 4 * ng;
+    uint8_t* vcb = seg + region(a.vc) + (size_t)(t0 + 32 * b) * 16 * bv;
+    uint8_t* vmb = seg + region(a.vm) + (size_t)(t0 + 32 * b) * 4 * ng;
     const uint32_t s = a.gv >= 32 ? quantize_values<false>(a, bv, vx, vcb, vmb, lane, wv)
                    : quantize_values<true>(a, bv, vx, vcb, vmb, lane, wv);
     most = max(most, s);
@@ -581,7 +581,7 @@ __device__ __forceinline__ void quantize_group(const AppendArgs& a, const Append
   }
 
   __syncthreads();
-  uint8_t* kdst = seg + a.kc + (size_t)t0 * 16 * bk;
+  uint8_t* kdst = seg + region(a.kc) + (size_t)t0 * 16 * bk;
   switch (bk) {
     case 1: key_codes<1, GK>(kx, par, kdst, lane, wv); break;
     case 2: key_codes<2, GK>(kx, par, kdst, lane, wv); break;
@@ -613,8 +613,8 @@ __device__ __forceinline__ void copy_ring(const AppendArgs& a, const AppendSeq& 
     const int idx = i * kAppendThreads + threadIdx.x, p = first + (idx >> 4);
     if (p < end) {
       const size_t dst = ((size_t)(p % a.W) * kHeadDim + (idx & 15) * 8) * 2;
-      *reinterpret_cast<u4_t*>(blk + a.tk + dst) = x[0][i];
-      *reinterpret_cast<u4_t*>(blk + a.tv + dst) = x[1][i];
+      *reinterpret_cast<u4_t*>(blk + region(a.tk) + dst) = x[0][i];
+      *reinterpret_cast<u4_t*>(blk + region(a.tv) + dst) = x[1][i];
     }
   }
 }

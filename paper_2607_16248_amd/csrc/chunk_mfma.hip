@@ -107,7 +107,7 @@ chunk_mfma_kernel(DecodeArgs a) {
   const DecodeSeq& S = a.seq[wk.si];
   const uint8_t* blk = a.arena + S.head0 + (uint64_t)wk.h * a.head_stride;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t vbound = __builtin_amdgcn_raw_buffer_load_b32(head_rsrc(blk + a.vb, 4), 0, 0, 0);
+  uint32_t vbound = __builtin_amdgcn_raw_buffer_load_b32(head_rsrc(blk + region(a.vb), 4), 0, 0, 0);
   asm volatile("" ::: "memory");
 
   if (wk.sp >= S.nq) {  // fp16 tail tokens; the reduction takes 8 rows at a time
@@ -166,8 +166,8 @@ chunk_mfma_kernel(DecodeArgs a) {
     int tok;
     const __amdgpu_buffer_rsrc_t r = seg_of(j * a.gk + (i % BPG) * 32, tok);
     const int jg = PAGED ? tok >> a.pm.gk_shift : j;
-    const uint32_t km = a.km + (uint32_t)jg * (2 * kHeadDim * 2), kc = a.kc + (uint32_t)tok * 16 * BK;
-    const uint32_t vc = a.vc + (uint32_t)(tok / 32) * 512 * BV, vm = a.vm + (uint32_t)(tok / 32) * vstride;
+    const uint32_t km = region(a.km) + (uint32_t)jg * (2 * kHeadDim * 2), kc = region(a.kc) + (uint32_t)tok * 16 * BK;
+    const uint32_t vc = region(a.vc) + (uint32_t)(tok / 32) * 512 * BV, vm = region(a.vm) + (uint32_t)(tok / 32) * vstride;
     o.s = ld32(r, lo_km, km);
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
@@ -204,7 +204,7 @@ chunk_mfma_kernel(DecodeArgs a) {
     const int j = j0 + kWaves * min(k0 + col, max(ngroups - 1, 0));
     if constexpr (PAGED) {
       const int tok = j * a.gk;
-      const uint8_t* zrow = pool_h + (uint64_t)ptab[tok >> a.pm.page_shift] * a.pm.page_bytes + a.km +
+      const uint8_t* zrow = pool_h + (uint64_t)ptab[tok >> a.pm.page_shift] * a.pm.page_bytes + region(a.km) +
                             (uint64_t)((tok & (a.pm.page_tokens - 1)) >> a.pm.gk_shift) * (2 * kHeadDim * 2) +
                             kHeadDim * 2;
 #pragma unroll
@@ -214,7 +214,7 @@ chunk_mfma_kernel(DecodeArgs a) {
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
         zq[kb] = __builtin_bit_cast(
-            h8_t, ld128(rs, (uint32_t)j * (2 * kHeadDim * 2) + kHeadDim * 2 + (32 * kb + 8 * row) * 2, a.km));
+            h8_t, ld128(rs, (uint32_t)j * (2 * kHeadDim * 2) + kHeadDim * 2 + (32 * kb + 8 * row) * 2, region(a.km)));
     }
   };
 

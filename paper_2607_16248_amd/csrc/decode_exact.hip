@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   auto load = [&](int i, ExactBlock<BK, BV>& o) {
     int t;
     const uint8_t* seg = a.arena + packed_seg(a.pm, S.head0, a.head_stride, S.seq, wk.h, token_of(i), t);
-    const uint8_t* kr = seg + a.kc + (size_t)t * 16 * BK + col * 16 * BK + blk * 4 * BK;
+    const uint8_t* kr = seg + region(a.kc) + (size_t)t * 16 * BK + col * 16 * BK + blk * 4 * BK;
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
       if constexpr (BK == 1) {
@@ -153,13 +153,13 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
         }
       }
     }
-    const uint8_t* km = seg + a.km + (size_t)(t >> gsh) * 512 + 16 * blk;
+    const uint8_t* km = seg + region(a.km) + (size_t)(t >> gsh) * 512 + 16 * blk;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       o.ks[kb] = *reinterpret_cast<const u4_t*>(km + 64 * kb);
       o.kz[kb] = *reinterpret_cast<const u4_t*>(km + 256 + 64 * kb);
     }
-    const uint8_t* vr = seg + a.vc + (size_t)(t >> 5) * 512 * BV + lane * 8 * BV;
+    const uint8_t* vr = seg + region(a.vc) + (size_t)(t >> 5) * 512 * BV + lane * 8 * BV;
     if constexpr (BV == 1) {
       const uint2 v = *reinterpret_cast<const uint2*>(vr);
       o.vx[0] = v.x;
@@ -176,14 +176,14 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   auto load_meta = [&](int i, ValueMeta<FINE>& o) {
     int t;
     const uint8_t* seg = a.arena + packed_seg(a.pm, S.head0, a.head_stride, S.seq, wk.h, token_of(i), t);
-    const uint8_t* vm = seg + a.vm + (size_t)(t >> 5) * 128 * ng;
+    const uint8_t* vm = seg + region(a.vm) + (size_t)(t >> 5) * 128 * ng;
 #pragma unroll
     for (int n = 0; n < (FINE ? 8 : 4); ++n) o.s[n] = *reinterpret_cast<const u4_t*>(vm + vgl[n]);
     o.zs = *reinterpret_cast<const u4_t*>(vm + zrow * 64 + 16 * blk);
     o.zz = *reinterpret_cast<const u4_t*>(vm + (ng + zrow) * 64 + 16 * blk);
   };
 
-  const int X = value_shift<BV>(*reinterpret_cast<const uint32_t*>(ring + a.vb) & 0xFFFFu);
+  const int X = value_shift<BV>(*reinterpret_cast<const uint32_t*>(ring + region(a.vb)) & 0xFFFFu);
   const h2_t vfac = operand_factor<BV>(X), kfac = operand_factor<BK>(0);
   // raw = alpha sum q z + beta sum q s + sum q K', score = ksc raw (q as held)
   constexpr float kAlpha = BK == 1 ? -2.f : 0.5f, kBeta = BK == 1 ? -1.f : Code<BK>::c0 * 0.5f;

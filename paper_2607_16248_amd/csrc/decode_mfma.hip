@@ -227,7 +227,7 @@ decode_mfma_kernel(DecodeArgs a) {
   // consumed after the query is prepared, so its latency hides behind the
   // first blocks' loads (a scalar load would be waited for with the loads of
   // the arguments, before those go out).
-  uint32_t vbound = __builtin_amdgcn_raw_buffer_load_b32(head_rsrc(blk + a.vb, 4), 0, 0, 0);
+  uint32_t vbound = __builtin_amdgcn_raw_buffer_load_b32(head_rsrc(blk + region(a.vb), 4), 0, 0, 0);
   asm volatile("" ::: "memory");
 
   if (wk.sp >= S.nq) {  // fp16 tail tokens
@@ -312,8 +312,8 @@ decode_mfma_kernel(DecodeArgs a) {
     int tok;
     const __amdgpu_buffer_rsrc_t r = seg_of(j * a.gk + (i % BPG) * 32, tok);
     const int jg = paged ? tok >> a.pm.gk_shift : j;  // key group within the segment
-    load_block<BK, BV, kFive>(r, lo, a.km + (uint32_t)jg * (2 * kHeadDim * 2), a.kc + (uint32_t)tok * 16 * BK,
-                       a.vc + (uint32_t)(tok / 32) * 512 * BV, a.vm + (uint32_t)(tok / 32) * vstride, o);
+    load_block<BK, BV, kFive>(r, lo, region(a.km) + (uint32_t)jg * (2 * kHeadDim * 2), region(a.kc) + (uint32_t)tok * 16 * BK,
+                       region(a.vc) + (uint32_t)(tok / 32) * 512 * BV, region(a.vm) + (uint32_t)(tok / 32) * vstride, o);
   };
   // Key zero-points of the wave's key groups k0 .. k0 + 15 as the A operand
   // of their zero-point terms (row = group; past the last group: the last).
@@ -322,7 +322,7 @@ decode_mfma_kernel(DecodeArgs a) {
     const int j = j0 + kWaves * min(k0 + col, ngroups - 1);
     if constexpr (PAGED) {
       const int tok = j * a.gk;
-      const uint8_t* zrow = pool_h + (uint64_t)ptab[tok >> a.pm.page_shift] * a.pm.page_bytes + a.km +
+      const uint8_t* zrow = pool_h + (uint64_t)ptab[tok >> a.pm.page_shift] * a.pm.page_bytes + region(a.km) +
                             (uint64_t)((tok & (a.pm.page_tokens - 1)) >> a.pm.gk_shift) * (2 * kHeadDim * 2) +
                             kHeadDim * 2;
 #pragma unroll
@@ -332,7 +332,7 @@ decode_mfma_kernel(DecodeArgs a) {
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
         zq[kb] = __builtin_bit_cast(
-            h8_t, ld128(rs, (uint32_t)j * (2 * kHeadDim * 2) + kHeadDim * 2 + (32 * kb + 8 * row) * 2, a.km));
+            h8_t, ld128(rs, (uint32_t)j * (2 * kHeadDim * 2) + kHeadDim * 2 + (32 * kb + 8 * row) * 2, region(a.km)));
     }
   };
   // The query heads this wave prepares for the workgroup (heads wv,

@@ -41,21 +41,21 @@ __global__ __launch_bounds__(128) void dequant_kernel(DequantArgs a) {
   if (p < a.Lq) {
     int q;  // p's position in its packed segment
     const uint8_t* seg = a.arena + packed_seg(a.pm, a.head0, a.head_stride, a.seq, h, p, q);
-    const uint16_t* km = reinterpret_cast<const uint16_t*>(seg + a.km) + (size_t)(q / a.gk) * 2 * kHeadDim;
-    const uint8_t* krow = seg + a.kc + (size_t)q * 16 * a.bk;
+    const uint16_t* km = reinterpret_cast<const uint16_t*>(seg + region(a.km)) + (size_t)(q / a.gk) * 2 * kHeadDim;
+    const uint8_t* krow = seg + region(a.kc) + (size_t)q * 16 * a.bk;
     const uint32_t kcode = key_code(krow, c, a.bk);
     kv = fmaf((float)kcode, h2f(km[c]), h2f(km[kHeadDim + c]));
     const int ng = kHeadDim / a.gv, g = c / a.gv;
-    const uint8_t* vblk = seg + a.vc + (size_t)(q / 32) * 512 * a.bv;
-    const uint8_t* vmb = seg + a.vm + (size_t)(q / 32) * 128 * ng;
+    const uint8_t* vblk = seg + region(a.vc) + (size_t)(q / 32) * 512 * a.bv;
+    const uint8_t* vmb = seg + region(a.vm) + (size_t)(q / 32) * 128 * ng;
     const int r = q % 32;
     vv = fmaf((float)value_code(vblk, r, c, a.bv),
               h2f(*reinterpret_cast<const uint16_t*>(vmb + value_meta_s(g, r))),
               h2f(*reinterpret_cast<const uint16_t*>(vmb + value_meta_z(g, r, ng))));
   } else {
     const size_t slot = (size_t)(p % a.W) * kHeadDim + c;
-    kv = h2f(reinterpret_cast<const uint16_t*>(blk + a.tk)[slot]);
-    vv = h2f(reinterpret_cast<const uint16_t*>(blk + a.tv)[slot]);
+    kv = h2f(reinterpret_cast<const uint16_t*>(blk + region(a.tk))[slot]);
+    vv = h2f(reinterpret_cast<const uint16_t*>(blk + region(a.tv))[slot]);
   }
   const size_t o = ((size_t)ti * a.hkv + h) * kHeadDim + c;
   a.K_out[o] = kv;
@@ -137,23 +137,23 @@ __global__ __launch_bounds__(256) void export_kernel(ExportArgs a) {
     for (int i = tid; i < n * 64; i += 256) {
       const int t = t0 + (i >> 6), d = i & 63;
       const size_t src = (size_t)((a.Lq + t) % a.W) * 64 + d, dst = (size_t)t * 64 + d;
-      reinterpret_cast<uint32_t*>(a.tk_out)[dst] = reinterpret_cast<const uint32_t*>(ring + a.tk)[src];
-      reinterpret_cast<uint32_t*>(a.tv_out)[dst] = reinterpret_cast<const uint32_t*>(ring + a.tv)[src];
+      reinterpret_cast<uint32_t*>(a.tk_out)[dst] = reinterpret_cast<const uint32_t*>(ring + region(a.tk))[src];
+      reinterpret_cast<uint32_t*>(a.tv_out)[dst] = reinterpret_cast<const uint32_t*>(ring + region(a.tv))[src];
     }
     return;
   }
   const int ng = kHeadDim / a.gv;
   int t;  // the block's first token in its packed segment
   const uint8_t* seg = a.arena + packed_seg(a.pm, a.head0, a.head_stride, a.seq, a.h, 32 * b, t);
-  const uint32_t* kc = reinterpret_cast<const uint32_t*>(seg + a.kc + (size_t)t * 16 * BK);
-  const uint32_t* vc = reinterpret_cast<const uint32_t*>(seg + a.vc + (size_t)t * 16 * BV);
-  const uint8_t* vm = seg + a.vm + (size_t)t * 4 * ng;
+  const uint32_t* kc = reinterpret_cast<const uint32_t*>(seg + region(a.kc) + (size_t)t * 16 * BK);
+  const uint32_t* vc = reinterpret_cast<const uint32_t*>(seg + region(a.vc) + (size_t)t * 16 * BV);
+  const uint8_t* vm = seg + region(a.vm) + (size_t)t * 4 * ng;
   uint32_t* kc_out = reinterpret_cast<uint32_t*>(a.kc_out + (size_t)b * 512 * BK);
   uint32_t* vc_out = reinterpret_cast<uint32_t*>(a.vc_out + (size_t)b * 512 * BV);
   uint32_t* vm_out = reinterpret_cast<uint32_t*>(a.vm_out) + (size_t)b * 32 * ng;
   if ((32 * b) % a.gk == 0 && tid < 128)  // a key group's scales and zeros: 512 bytes
     reinterpret_cast<uint32_t*>(a.km_out)[(size_t)(32 * b / a.gk) * 128 + tid] =
-        reinterpret_cast<const uint32_t*>(seg + a.km)[(size_t)(t / a.gk) * 128 + tid];
+        reinterpret_cast<const uint32_t*>(seg + region(a.km))[(size_t)(t / a.gk) * 128 + tid];
   for (int i = tid; i < 32 * BV; i += 256) reinterpret_cast<uint4*>(vblk)[i] = reinterpret_cast<const uint4*>(vc)[i];
   for (int i = tid; i < 128 * BK; i += 256) kc_out[i] = canonical_key<BK>(kc + i / (4 * BK) * (4 * BK), i % (4 * BK));
   for (int i = tid; i < 32 * ng; i += 256) {

@@ -477,8 +477,8 @@ kvq_status kvq_append(kvq_cache* c, const void* K, const void* V, int32_t n_max,
       a.K = static_cast<const uint16_t*>(K);
       a.V = static_cast<const uint16_t*>(V);
       a.head_stride = lay.stride;
-      a.kc = (uint32_t)lay.kc; a.km = (uint32_t)lay.km; a.vc = (uint32_t)lay.vc;
-      a.vm = (uint32_t)lay.vm; a.tk = (uint32_t)lay.tk; a.tv = (uint32_t)lay.tv; a.vb = (uint32_t)lay.vb;
+      a.kc = kvq::region_units(lay.kc); a.km = kvq::region_units(lay.km); a.vc = kvq::region_units(lay.vc);
+      a.vm = kvq::region_units(lay.vm); a.tk = kvq::region_units(lay.tk); a.tv = kvq::region_units(lay.tv); a.vb = kvq::region_units(lay.vb);
       a.n_max = n_max; a.hkv = d.num_kv_heads; a.gk = d.key_group; a.gv = d.value_group; a.W = c->W;
       a.quantize = quant ? 1 : 0;
       a.pm = c->pm;
@@ -726,8 +726,8 @@ kvq_status run_partials(const kvq_cache* c, const SplitPlan& p, const void* q, v
     a.q = static_cast<const uint16_t*>(q);
     a.ws = static_cast<float*>(ws);
     a.head_stride = lay.stride;
-    a.kc = (uint32_t)lay.kc; a.km = (uint32_t)lay.km; a.vc = (uint32_t)lay.vc;
-    a.vm = (uint32_t)lay.vm; a.tk = (uint32_t)lay.tk; a.tv = (uint32_t)lay.tv; a.vb = (uint32_t)lay.vb;
+    a.kc = kvq::region_units(lay.kc); a.km = kvq::region_units(lay.km); a.vc = kvq::region_units(lay.vc);
+    a.vm = kvq::region_units(lay.vm); a.tk = kvq::region_units(lay.tk); a.tv = kvq::region_units(lay.tv); a.vb = kvq::region_units(lay.vb);
     a.hq = d.num_q_heads; a.hkv = d.num_kv_heads; a.gk = d.key_group; a.gv = d.value_group; a.W = c->W;
     a.split_tokens = p.st[cls.second[0]];
     a.qscale = qscale;
@@ -931,8 +931,8 @@ kvq_status kvq_dequant(const kvq_cache* c, int32_t seq, int32_t tok0, int32_t nt
   a.pm = c->pm;
   a.K_out = K_out; a.V_out = V_out;
   a.head_stride = lay.stride;
-  a.kc = (uint32_t)lay.kc; a.km = (uint32_t)lay.km; a.vc = (uint32_t)lay.vc;
-  a.vm = (uint32_t)lay.vm; a.tk = (uint32_t)lay.tk; a.tv = (uint32_t)lay.tv;
+  a.kc = kvq::region_units(lay.kc); a.km = kvq::region_units(lay.km); a.vc = kvq::region_units(lay.vc);
+  a.vm = kvq::region_units(lay.vm); a.tk = kvq::region_units(lay.tk); a.tv = kvq::region_units(lay.tv);
   a.hkv = c->d.num_kv_heads; a.gk = c->d.key_group; a.gv = c->d.value_group; a.W = c->W;
   a.bk = c->bk[seq]; a.bv = c->bv[seq]; a.Lq = c->Lq[seq]; a.tok0 = tok0; a.ntok = ntok;
   const int e = kvq::launch_dequant(a, stream);
@@ -967,8 +967,8 @@ kvq_status kvq_export(const kvq_cache* c, int32_t seq, int32_t h, void* dst, siz
   x.vm_out = x.vc_out + Lq * 16 * c->bv[seq];
   x.tk_out = x.vm_out + Lq * (D / c->d.value_group) * 4;
   x.tv_out = x.tk_out + tail * D * 2;
-  x.kc = (uint32_t)lay.kc; x.km = (uint32_t)lay.km; x.vc = (uint32_t)lay.vc;
-  x.vm = (uint32_t)lay.vm; x.tk = (uint32_t)lay.tk; x.tv = (uint32_t)lay.tv;
+  x.kc = kvq::region_units(lay.kc); x.km = kvq::region_units(lay.km); x.vc = kvq::region_units(lay.vc);
+  x.vm = kvq::region_units(lay.vm); x.tk = kvq::region_units(lay.tk); x.tv = kvq::region_units(lay.tv);
   x.bk = c->bk[seq]; x.bv = c->bv[seq]; x.gk = c->d.key_group; x.gv = c->d.value_group; x.W = c->W;
   x.Lq = (int32_t)Lq; x.ntail = (int32_t)tail; x.seq = seq; x.h = h;
   x.pm = c->pm;

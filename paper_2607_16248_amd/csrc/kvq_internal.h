@@ -33,6 +33,15 @@ constexpr uint64_t kHeaderBytes = 256;
 
 inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
+// The kernels' arguments hold region offsets in units of kAlign: 32 bits reach
+// 1 TiB, more than the largest head (2^31 - 1 tokens) has.
+inline uint32_t region_units(uint64_t offset) { return (uint32_t)(offset / kAlign); }
+#ifdef __HIPCC__
+__host__ __device__ inline uint64_t region(uint32_t units) { return (uint64_t)units * kAlign; }
+#else
+inline uint64_t region(uint32_t units) { return (uint64_t)units * kAlign; }
+#endif
+
 struct HeadLayout {
   uint64_t kc, km, vc, vm, tk, tv;  // byte offsets inside a (seq, head) block
   uint64_t vb;                      // bound on the value scales packed so far (fp16 bits, in a uint32)
@@ -119,7 +128,7 @@ struct AppendArgs {
   const uint16_t* K;  // fp16 [batch][n_max][Hkv][128]
   const uint16_t* V;
   uint64_t head_stride;
-  uint32_t kc, km, vc, vm, tk, tv, vb;
+  uint32_t kc, km, vc, vm, tk, tv, vb;  // in region_units
   int32_t n_max, hkv, gk, gv, W, nseq, total_wg;
   int32_t quantize;   // 1: pack groups in this launch
   PageMap pm;
@@ -158,7 +167,7 @@ struct DecodeArgs {
   const uint16_t* V_new;
   int32_t n_max, pad;
   uint64_t head_stride;
-  uint32_t kc, km, vc, vm, tk, tv, vb;
+  uint32_t kc, km, vc, vm, tk, tv, vb;  // in region_units
   int32_t hq, hkv, gk, gv, W, split_tokens, nseq, total_wg;
   float qscale;       // log2(e) / sqrt(d)
   DecodeSeq seq[kMaxSeqPerLaunch];
@@ -221,7 +230,7 @@ struct DequantArgs {
   float* K_out;
   float* V_out;
   uint64_t head_stride;
-  uint32_t kc, km, vc, vm, tk, tv;
+  uint32_t kc, km, vc, vm, tk, tv;  // in region_units
   int32_t hkv, gk, gv, W, bk, bv, Lq, tok0, ntok;
   int32_t seq;
   PageMap pm;
@@ -242,7 +251,7 @@ struct ExportArgs {
   uint8_t* vm_out;      // value meta [Lq][128/gv][2] fp16
   uint8_t* tk_out;      // key tail [ntail][128] fp16
   uint8_t* tv_out;      // value tail [ntail][128] fp16
-  uint32_t kc, km, vc, vm, tk, tv;
+  uint32_t kc, km, vc, vm, tk, tv;  // in region_units
   int32_t bk, bv, gk, gv, W, Lq, ntail, seq, h;
   PageMap pm;
 };

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int wave_limit = active ? seen0 + min(rg * a.qpr + a.qpr - 1, a.nqry - 1) : 0;
 
   const uint8_t* ring = a.arena + S.head0 + (uint64_t)h * a.head_stride;
-  const uint32_t vbits = *reinterpret_cast<const uint32_t*>(ring + a.vb) & 0xFFFFu;
+  const uint32_t vbits = *reinterpret_cast<const uint32_t*>(ring + region(a.vb)) & 0xFFFFu;
 
   // row g of a row group: query x of the group (one past the last for the
   // rows beyond whole queries) and query head, without a lane-wise read of
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   auto load_key = [&](int b, Staged& o) {
     int tin;
     const __amdgpu_buffer_rsrc_t r = seg_of(b, tin);
-    const uint32_t kc = a.kc + (uint32_t)tin * 16 * BK;
+    const uint32_t kc = region(a.kc) + (uint32_t)tin * 16 * BK;
     if constexpr (BK == 8) {
       const uint2 v = ld64(r, lo_k, kc);
       o.x[0] = v.x;
@@ -182,12 +182,12 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     } else {
       o.x[0] = ld32(r, lo_k, kc);
     }
-    o.s = ld128(r, lo_ks, a.km + (uint32_t)(tin >> gsh) * 512);
+    o.s = ld128(r, lo_ks, region(a.km) + (uint32_t)(tin >> gsh) * 512);
   };
   auto load_value = [&](int b, Staged& o) {
     int tin;
     const __amdgpu_buffer_rsrc_t r = seg_of(b, tin);
-    const uint32_t vc = a.vc + (uint32_t)(tin / 32) * 512 * BV, vm = a.vm + (uint32_t)(tin / 32) * 128 * ng;
+    const uint32_t vc = region(a.vc) + (uint32_t)(tin / 32) * 512 * BV, vm = region(a.vm) + (uint32_t)(tin / 32) * 128 * ng;
     if constexpr (BV == 8) {
       const uint2 v = ld64(r, lo_v, vc);
       o.x[0] = v.x;
@@ -237,9 +237,9 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     k = v = (u4_t){0u, 0u, 0u, 0u};
     const int t = 32 * b + 16 * kmb + col;
     if (t < S.L)
-      k = *reinterpret_cast<const u4_t*>(ring + a.tk + ((size_t)(t % a.W) * kHeadDim + 32 * kkb + 8 * blk) * 2);
+      k = *reinterpret_cast<const u4_t*>(ring + region(a.tk) + ((size_t)(t % a.W) * kHeadDim + 32 * kkb + 8 * blk) * 2);
     if constexpr (BK == 1) k ^= 0x80008000u;
-    const uint16_t* rv = reinterpret_cast<const uint16_t*>(ring + a.tv) + 16 * wv + col;
+    const uint16_t* rv = reinterpret_cast<const uint16_t*>(ring + region(a.tv)) + 16 * wv + col;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int tv = 32 * b + (e < 4 ? 4 * blk + e : 12 + 4 * blk + e);
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
                                      (uint64_t)a.pm.table[(size_t)S.seq * a.pm.max_pages + pg] * a.pm.page_bytes +
                                      (uint64_t)h * a.pm.page_head_bytes
                                : ring;
-    zreg = *reinterpret_cast<const u4_t*>(seg + a.km + (size_t)(tin >> gsh) * 512 + (threadIdx.x & 31) * 16);
+    zreg = *reinterpret_cast<const u4_t*>(seg + region(a.km) + (size_t)(tin >> gsh) * 512 + (threadIdx.x & 31) * 16);
   };
   auto store_zs = [&]() {
     *reinterpret_cast<u4_t*>(&sm.zs[(threadIdx.x >> 5) * kZRow + (threadIdx.x & 31) * 4]) = zreg;

@@ -79,8 +79,8 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
   const int n_new = a.K_new != nullptr ? S.L - S.L_old : 0;
   const size_t new0 = ((size_t)S.seq * a.n_max * a.hkv + h) * kHeadDim, new_stride = (size_t)a.hkv * kHeadDim;
   if (n_new > 0) {
-    uint32_t* rk = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(ring) + a.tk);
-    uint32_t* rv = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(ring) + a.tv);
+    uint32_t* rk = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(ring) + region(a.tk));
+    uint32_t* rv = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(ring) + region(a.tv));
     constexpr int kRow = kHeadDim / 2;  // dwords per token row
     for (int idx = threadIdx.x; idx < n_new * kRow; idx += blockDim.x) {
       const int t = idx / kRow, c = idx % kRow;
@@ -91,11 +91,11 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
   }
   const int ntail = S.L - S.Lq, slot0 = S.Lq % a.W;
   // the row of tail token i (past the last: the last), in the ring or the inputs
-  auto row_at = [&](int i, const uint16_t* in, uint32_t region) -> const uint16_t* {
+  auto row_at = [&](int i, const uint16_t* in, uint64_t at) -> const uint16_t* {
     i = min(i, ntail - 1);
     int slot = slot0 + i;
     slot = slot >= a.W ? slot - a.W : slot;
-    const uint16_t* r = reinterpret_cast<const uint16_t*>(ring + region) + slot * kHeadDim;
+    const uint16_t* r = reinterpret_cast<const uint16_t*>(ring + at) + (size_t)slot * kHeadDim;
     if (n_new > 0 && i >= ntail - n_new) r = in + new0 + (size_t)(i - (ntail - n_new)) * new_stride;
     return r;
   };
@@ -106,7 +106,7 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
     f4_t d[NT][2];
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
-      const uint16_t* kr = row_at(32 * b + 16 * mb + col, a.K_new, a.tk) + 8 * blk;
+      const uint16_t* kr = row_at(32 * b + 16 * mb + col, a.K_new, region(a.tk)) + 8 * blk;
       u4_t k[4];
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) k[kb] = *reinterpret_cast<const u4_any*>(kr + 32 * kb);
@@ -120,7 +120,7 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
     }
     const uint16_t* vr[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) vr[e] = row_at(32 * b + value_token(blk, e), a.V_new, a.tv) + col;
+    for (int e = 0; e < 8; ++e) vr[e] = row_at(32 * b + value_token(blk, e), a.V_new, region(a.tv)) + col;
     h8_t ph[NT], pl[NT];
 #pragma unroll
     for (int u = 0; u < NT; ++u) {

@@ -35,8 +35,28 @@ hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKin
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 
+// The regions of a head in the order of the layout, none starting before the
+// one ahead of it ends: vb is the last, one alignment unit before the head's
+// end.  (A page holds the packed regions, the ring's block the others.)
+template <class Args>
+static void check_regions(const Args& a, const uint32_t* vb_units) {
+  const uint64_t kc = kvq::region(a.kc), km = kvq::region(a.km), vc = kvq::region(a.vc), vm = kvq::region(a.vm),
+                 tk = kvq::region(a.tk), tv = kvq::region(a.tv),
+                 ring = kvq::align_up((uint64_t)a.W * kvq::kHeadDim * 2, kvq::kAlign),
+                 vb = vb_units ? kvq::region(*vb_units) : tv + ring,
+                 packed_end = a.pm.table != nullptr ? a.pm.page_head_bytes : tk;
+  if (kc <= km && km <= vc && vc <= vm && vm <= packed_end && tv - tk == ring && vb - tv == ring &&
+      vb + kvq::kAlign == a.head_stride)
+    return;
+  std::fprintf(stderr, "region check failed: kc %llx km %llx vc %llx vm %llx tk %llx tv %llx vb %llx, stride %llx\n",
+               (unsigned long long)kc, (unsigned long long)km, (unsigned long long)vc, (unsigned long long)vm,
+               (unsigned long long)tk, (unsigned long long)tv, (unsigned long long)vb,
+               (unsigned long long)a.head_stride);
+  std::abort();
+}
+
 namespace kvq {
-int launch_append(const AppendArgs&, int, int, void*) { return ++g_launches, 0; }
+int launch_append(const AppendArgs& a, int, int, void*) { return check_regions(a, &a.vb), ++g_launches, 0; }
 int launch_table_set(const TableSet& t, void*) {
   // the table lives in the arena: write it as the kernel would
   for (int i = 0; i < t.n; ++i) t.table[t.idx[i]] = t.val[i];
@@ -54,6 +74,7 @@ int launch_word_reset(const WordReset& r, void*) {
 // sequence's [nqry][Hq] block, every record row in [0, nqry * Hq), and every
 // (query, head) of a kv head is written by exactly one row.
 static void check_rows(const kvq::DecodeArgs& a, int rows) {
+  check_regions(a, &a.vb);
   if (a.nqry <= 1) return;
   auto bad = [&](const char* what, int rg, int g) {
     std::fprintf(stderr, "row check failed (%s): nqry %d qpr %d nrg %d gqh %d rows %d, group %d row %d\n", what,
@@ -86,10 +107,10 @@ namespace kvq {
 int launch_decode(const DecodeArgs& a, int, int, int rows, void*) { return check_rows(a, rows), ++g_launches, 0; }
 int launch_decode_matrix(const DecodeArgs& a, int, int, int rows, void*) { return check_rows(a, rows), ++g_launches, 0; }
 int launch_chunk_matrix(const DecodeArgs& a, int, int, int rows, void*) { return check_rows(a, rows), ++g_launches, 0; }
-int launch_export(const ExportArgs&, void*) { return ++g_launches, 0; }
+int launch_export(const ExportArgs& a, void*) { return check_regions(a, nullptr), ++g_launches, 0; }
 int launch_merge(const MergeArgs&, void*) { return ++g_launches, 0; }
 int launch_dgap(const DgapArgs&, int, void*) { return ++g_launches, 0; }
-int launch_dequant(const DequantArgs&, void*) { return ++g_launches, 0; }
+int launch_dequant(const DequantArgs& a, void*) { return check_regions(a, nullptr), ++g_launches, 0; }
 int launch_fill_zero(void* dst, size_t words, void*) {
   std::memset(dst, 0, words * 4);
   return ++g_launches, 0;

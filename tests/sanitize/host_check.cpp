@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <sys/mman.h>
 #include <vector>
 
 #include "dgap.h"
@@ -145,6 +146,33 @@ static void exercise(const kvq_cache_desc& d) {
   kvq_cache_destroy(c);
 }
 
+// A head whose value scales and fp16 ring lie past 4 GiB (the launch
+// stand-ins check the order of the regions).  The arena is reserved, never
+// filled.
+static void large_head(int bits_k, int bits_v, int gv, int max_tokens, int window, int page) {
+  const uint8_t bk[1] = {(uint8_t)bits_k}, bv[1] = {(uint8_t)bits_v};
+  const kvq_cache_desc d = desc(1, 4, 1, max_tokens, 32, gv, window, bk, bv, page, page ? 4 : 0);
+  const size_t bytes = kvq_cache_bytes(&d);
+  EXPECT(bytes > ((size_t)1 << 32));
+  void* arena = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  EXPECT(arena != MAP_FAILED);
+  if (arena == MAP_FAILED) return;
+  kvq_cache* c = nullptr;
+  EXPECT(kvq_cache_init(&c, &d, arena, bytes) == KVQ_OK);
+  const int32_t n = 100;
+  Buf kv((size_t)n * 128 * 2), q((size_t)40 * 4 * 128 * 2), out((size_t)40 * 4 * 128 * 4), ko((size_t)n * 128 * 4);
+  EXPECT(kvq_append(c, kv.p, kv.p, n, &n, nullptr) == KVQ_OK);
+  Buf ws(kvq_chunk_workspace_bytes(c, 40));
+  EXPECT(kvq_decode_attention(c, q.p, out.as<float>(), ws.p, ws.n, nullptr) == KVQ_OK);
+  EXPECT(kvq_chunk_attention(c, q.p, 3, out.as<float>(), ws.p, ws.n, nullptr) == KVQ_OK);
+  EXPECT(kvq_chunk_attention(c, q.p, 40, out.as<float>(), ws.p, ws.n, nullptr) == KVQ_OK);
+  EXPECT(kvq_dequant(c, 0, 0, n, ko.as<float>(), ko.as<float>(), nullptr) == KVQ_OK);
+  Buf img(kvq_export_bytes(c, 0, 0));
+  EXPECT(kvq_export(c, 0, 0, img.p, img.n, nullptr) == KVQ_OK);
+  kvq_cache_destroy(c);
+  munmap(arena, bytes);
+}
+
 int main() {
   const uint8_t b1[4] = {1, 1, 1, 1}, b2[4] = {2, 2, 2, 2}, mixk[4] = {1, 2, 4, 8}, mixv[4] = {2, 1, 8, 4},
                 b4[4] = {4, 4, 4, 4}, b8[4] = {8, 8, 8, 8};
@@ -178,6 +206,10 @@ int main() {
   exercise(desc(3, 32, 8, 900, 32, 32, 0, b8, b8, 64));        // paged
   exercise(desc(2, 32, 8, 800, 32, 32, 50, b1, b1, 128, 9));   // paged, shared pool smaller than capacity
   exercise(desc(1, 8, 8, 200, 32, 128, 0, b1, b1));            // one head per kv head
+  large_head(8, 8, 32, 1 << 24, 0, 0);
+  large_head(2, 2, 8, 1 << 25, 0, 0);
+  large_head(8, 1, 128, 1 << 24, 1 << 23, 0);
+  large_head(1, 1, 32, 1 << 26, (1 << 24) + 5, 64);  // paged: a ring past 4 GiB
   // DGAP argument checks
   {
     EXPECT(dgap_workspace_bytes(1, 32768, 64) > 0);

@@ -14,6 +14,7 @@ import pytest
 
 import oracle
 from helpers import Case, log, row_rel_err
+from paper_2607_16248_amd import kvq
 from workloads import Workload, gen_q_chunk
 
 torch = pytest.importorskip("torch")
@@ -71,4 +72,43 @@ def test_ranges(bk, bv, gv, scale):
     c.append_all()
     err = row_rel_err(c.decode()[0], c.oracle_out(0)).max()
     log(f"[exact] {w.name} scale {scale:g}: {err:.2e}")
+    assert err <= TOL
+
+
+def _quantized(x, dim, bits):
+    """Min-max quantized and dequantized along dim, in float64: the smallest fp16 scale that covers the range."""
+    lo, hi = x.amin(dim, keepdim=True), x.amax(dim, keepdim=True)
+    want = (hi - lo) / (2 ** bits - 1)
+    s = want.half()
+    s = torch.where(s.double() < want, (s.view(torch.int16) + 1).view(torch.half), s).double()
+    return lo + s * torch.where(s > 0, (x - lo) / s, 0.0).round()
+
+
+def test_head_past_4gib():
+    """8-bit keys and values with room for 2^24 tokens: the value scales and the fp16 ring lie past 4 GiB.  The key
+    codes of the tokens from 2^21 on reach the offsets that those would have modulo 2^32."""
+    n, room = (1 << 21) + 4096 + 5, 1 << 24
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    K, V = (torch.randn((1, n, 1, 128), generator=gen, device="cuda", dtype=torch.half) for _ in range(2))
+    q = torch.randn((1, 4, 128), generator=gen, device="cuda", dtype=torch.half)
+    cache = kvq.KVCache(1, 4, 1, room, [8], [8], key_group=32, value_group=32, fp16_window=0)
+    cache.append(K, V, [n])
+    kd, vd = cache.dequant(0, 0, n)
+    lq = n // 32 * 32
+    for t0, t1 in ((0, 4096), (1 << 20, (1 << 20) + 4096), (1 << 21, lq)):
+        k = K[0, t0:t1, 0].double().view(-1, 32, 128)
+        v = V[0, t0:t1, 0].double().view(-1, 4, 32)
+        assert (kd[t0:t1, 0].double() - _quantized(k, 1, 8).view(-1, 128)).abs().max() <= 2.0 ** -21  # |x| < 8 in fp32
+        assert (vd[t0:t1, 0].double() - _quantized(v, 2, 8).view(-1, 128)).abs().max() <= 2.0 ** -21
+    assert (kd[lq:, 0] == K[0, lq:, 0].float()).all() and (vd[lq:, 0] == V[0, lq:, 0].float()).all()
+    out = cache.decode(q)[0].double()
+    s = torch.empty((4, n), device="cuda", dtype=torch.double)
+    for t in range(0, n, 1 << 18):
+        s[:, t:t + (1 << 18)] = q[0].double() @ kd[t:t + (1 << 18), 0].double().t().contiguous()
+    p = torch.softmax(s / 128 ** 0.5, 1)
+    ref, size = (sum(p[:, t:t + (1 << 18)].contiguous() @ f(vd[t:t + (1 << 18), 0].double()) for t in range(0, n, 1 << 18))
+                 for f in (torch.clone, torch.abs))
+    # the bound is on the terms' sum of magnitudes: over two million tokens the values themselves average out
+    err = ((out - ref).abs().amax(1) / size.amax(1)).max().item()
+    log(f"[exact] {n} tokens of a head past 4 GiB: {err:.2e}")
     assert err <= TOL
