@@ -13,8 +13,8 @@
 // four and eight bits, whose products take two fp16 parts, hi = fl(x) and
 // lo = x - hi.  One bit has K' = s (1 - 2 code), the scale with the code as
 // its sign bit: score = sum_c q (z + s/2) - 1/2 sum_c q K'.  q enters as the
-// fp16 it is, p as fp16 (weights up to 2^14) for the packed values' product and
-// as hi + lo for the zero-point terms, the denominator and the fp16 tail.
+// fp16 it is, p as hi + lo halves (weights up to 2^14); only the packed values'
+// product at four and eight bits takes the hi half alone.
 //
 // Both products are transposed, so that the first one's output is the second
 // one's operand without a lane exchange:
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int t = 0; t < 8; ++t) v8[t] = __builtin_bit_cast(h8_t, op[8 * PK + t][lane]);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto values = [&](int b) {
+  auto values = [&](auto lows_c, int b) {
     const u4_t(*op)[64] = sm.op[b & (kSlots - 1)];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -404,6 +404,10 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
       const h8_t v = t < 8 ? v8[t] : __builtin_bit_cast(h8_t, op[8 * PK + t][lane]);
 #pragma unroll
       for (int u = 0; u < 2; ++u) acc[u][t / PV] = mfma(v, ph[u], acc[u][t / PV]);
+      if (decltype(lows_c)::value && t % PV == 0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) acc[u][t / PV] = mfma(v, pl[u], acc[u][t / PV]);
+      }
     }
   };
 
@@ -456,7 +460,7 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   // a step earlier; a barrier before every second step then keeps each
   // buffer's writes two steps away from its reads on both sides.  Past the
   // last block everything repeats it or goes unused.
-  if (b0 < bp) {
+  auto packed_blocks = [&](auto lows_c) {
     const int last = bp - 1;
     Staged sk, sv;
     {
@@ -500,19 +504,30 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (; b < bv; ++b) {
       begin(b);
       softmax(no, yes, b, d, [&] { scores(b + 1, d); fetch(b); });
-      values(b);
+      values(lows_c, b);
       refill(b);
     }
     for (; b < bm; ++b) {
       begin(b);
       softmax(yes, yes, b, d, [&] { scores(b + 1, d); fetch(b); });
-      values(b);
+      values(lows_c, b);
       refill(b);
     }
     for (; b < bp; ++b) {
       begin(b);
       refill(b);
     }
+  };
+  // Weights of one half (11 bits) leave a row 1e-4 off.  At one and two bits the
+  // smaller row groups are closer where one token leads the softmax (prompts
+  // up to some thousand tokens: 5e-5 to 1e-4 against 1.2e-4 to 1.9e-4), so the
+  // low halves join (5e-7 to 1e-6; 8192 tokens 120 us, 105 without them).  At
+  // four and eight bits the smaller groups are at 1.6e-4 to 2.9e-4 themselves,
+  // and the low halves matter only where the scales are subnormal: their
+  // rounding leaves codes unused, and the products are lopsided.
+  if (b0 < bp) {
+    if (PV == 1 || vbits < 0x0400u) packed_blocks(yes);
+    else packed_blocks(no);
   }
   float unit_acc = unit_packed;  // factor of the value accumulators
   if (max(b0, nb_packed) < b1) {

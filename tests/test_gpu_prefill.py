@@ -183,3 +183,33 @@ def test_zero_points_of_packed_tokens(gq, bits, gv):
     err = row_rel_err(out[0], oracle.chunk_seq(q[0], c.K[0], c.V[0], bits[0], bits[1], 32, gv, 0)).max()
     log(f"[prefill] {c.w.name}: {err:.2e}")
     assert err <= 2.0 ** -18
+
+
+# Packed tokens: at one and two bits both halves of the weights meet the values,
+# so what is left are fp32 sums (2^-24 per addition over up to 2^8 blocks and
+# scores of magnitude up to 2^5): 2^-17.
+@pytest.mark.parametrize("gq,bits,gv,n_q,L", [(4, (1, 1), 32, 100, 2000), (4, (1, 2), 32, 64, 320), (5, (2, 1), 64, 40, 1500),
+                                              (8, (2, 2), 128, 33, 3000), (1, (2, 2), 32, 300, 700)])
+def test_packed_tokens_meet_both_halves_of_the_weights(gq, bits, gv, n_q, L):
+    c = Case(W(f"packed_gq{gq}_K{bits[0]}V{bits[1]}_L{L}", 2 * gq, 2, (L,), bits[0], bits[1], gv=gv))
+    c.append_all()
+    q, out = _run(c, n_q)
+    err = row_rel_err(out[0], oracle.chunk_seq(q[0], c.K[0], c.V[0], bits[0], bits[1], 32, gv, 0)).max()
+    log(f"[prefill] {c.w.name} n_q {n_q}: {err:.2e}")
+    assert err <= 2.0 ** -17
+
+
+# Value ranges of a few subnormal steps: the scale is the smallest there is, half
+# of the codes or more go unused, and a value is the difference of its
+# zero-point with the scale's multiple (up to 2^7 steps) and its product (as
+# much), where the row's largest output has about 2^3 steps: 2^4 times the bound
+# above.
+@pytest.mark.parametrize("bits,scale", [((8, 8), 2.0 ** -20), ((4, 8), 2.0 ** -21), ((8, 4), 2.0 ** -23)])
+def test_subnormal_value_scales(bits, scale):
+    c = Case(W(f"steps_K{bits[0]}V{bits[1]}_{scale:.0e}", 16, 2, (512,), bits[0], bits[1]))
+    c.V[0] = (c.V[0].astype(np.float32) * scale).astype(np.float16)
+    c.append_all()
+    q, out = _run(c, 48)
+    err = row_rel_err(out[0], oracle.chunk_seq(q[0], c.K[0], c.V[0], bits[0], bits[1], 32, 32, 0)).max()
+    log(f"[prefill] {c.w.name}: {err:.2e}")
+    assert err <= 2.0 ** -13
