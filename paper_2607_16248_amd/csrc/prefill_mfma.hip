@@ -78,6 +78,7 @@ struct PrefillSmem {
   u4_t op[kSlots][kOps][64];
   uint32_t zs[kZGroups * kZRow];
   float dz[kNW][kZGroups][32];
+  uint32_t raw[kNW];  // fp16 tail: whether the value tile's operand is as it is (else lifted)
 };
 
 // What a wave holds of a block between its loads and the unpacking: its key
@@ -412,10 +413,12 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
   };
 
   // fp16 tail: both halves of the weights meet the raw values (the product the
-  // other chunk kernels' tails make, tail_mfma.h), which enter lifted while they
-  // are small.  A tail is a window and a key group long, so its blocks are few.
+  // other chunk kernels' tails make, tail_mfma.h), which the wave that loads them
+  // lifts while they are small.  A tail is a window and a key group long, so its
+  // blocks are few.
   auto tail_values = [&](int b, uint32_t& raw) {
     const u4_t(*op)[64] = sm.op[b & (kSlots - 1)];
+    const uint32_t now = (uint32_t)__builtin_amdgcn_ballot_w64(lane < kNW && sm.raw[lane & (kNW - 1)] != 0u);
     const h8_t ones = __builtin_bit_cast(h8_t, op[kZOp][lane]);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -425,16 +428,15 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const u4_t w = op[8 * PK + t * PV][lane];
-      if (!((raw >> t) & 1u) && needs_raw(w)) {
-        raw |= 1u << t;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) acc[u][t] *= 1.f / kLift;
-      }
       f4_t x[2] = {acc[0][t], acc[1][t]};
-      if ((raw >> t) & 1u) {
+      if ((now >> t) & 1u) {
+        if (!((raw >> t) & 1u)) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u) x[u] *= 1.f / kLift;
+        }
         add_raw<2>(w, ph, pl, x);
       } else {
-        const h8_t v = lifted(w, false);
+        const h8_t v = __builtin_bit_cast(h8_t, w);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           x[u] = mfma(v, ph[u], x[u]);
@@ -444,6 +446,7 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
       acc[0][t] = x[0];
       acc[1][t] = x[1];
     }
+    raw = now;
   };
 
   // the constant part of the operand [z; s; 1; z']
@@ -537,14 +540,17 @@ __global__ __launch_bounds__(64 * kNW) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
       for (int t = 0; t < 8; ++t) acc[u][t] *= unit_acc * kLift;
     unit_acc = 1.f;
-    uint32_t raw = 0u;  // bit t: the values of tile t enter as they are, no longer lifted
+    uint32_t raw = 0u;  // bit t: the accumulators of tile t are no longer lifted
+    bool own_raw = false;  // this wave's value tile met a number of 8 or more
     const u4_t none = {0u, 0u, 0u, 0u};
     u4_t k, v;
     load_tail(max(b0, nb_packed), k, v);
     for (int b = max(b0, nb_packed); b < b1; ++b) {
       __syncthreads();  // every wave is done with the buffer
       put_key(b, k, none);
-      put_value(b, v, none);
+      own_raw = own_raw || needs_raw(v);
+      if (lane == 0) sm.raw[wv] = own_raw ? 1u : 0u;
+      put_value(b, __builtin_bit_cast(u4_t, lifted(v, own_raw)), none);
       put_zz(b, 0u);
       if (b + 1 < b1) load_tail(b + 1, k, v);
       __syncthreads();
