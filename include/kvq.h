@@ -187,10 +187,16 @@ kvq_status kvq_append_decode(kvq_cache* cache, const void* K, const void* V, int
  * results themselves (for example across devices) and for timing.
  * kvq_decode_partials writes, for every sequence i, query head h and split
  * k, one record of 132 floats at ws + ((base_i + k) * Hq + h) * 132:
- *   [0] m = max over the split's tokens of the base-2 score
+ *   [0] m = the reference of the split's base-2 scores
  *       log2(e) * q.k / sqrt(d),  [1] l = sum of 2^(score - m),
  *   [2..3] unused,  [4..131] acc[c] = sum of 2^(score - m) * V^[c],
- * where base_i is the number of splits of sequences 0..i-1.  The split plan
+ * where base_i is the number of splits of sequences 0..i-1.  m is the
+ * maximum of the scores in the split of the fp16 tokens (the last one of a
+ * sequence that has such tokens), and in every split where one of the two
+ * widths is 1 or 2 bits and the other 4 or 8, or value groups have 8 or 16
+ * channels.  In the packed splits of the other classes it lies between 15
+ * below the maximum and 3 above it: records combine through m, which is no
+ * maximum of its own there.  The split plan
  * depends only on the lengths and the split setting.  kvq_decode_merge
  * reads those records and writes out exactly as kvq_decode_attention does;
  * no append may come between the two calls. */

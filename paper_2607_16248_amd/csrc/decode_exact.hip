@@ -189,7 +189,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   constexpr float kAlpha = BK == 1 ? -2.f : 0.5f, kBeta = BK == 1 ? -1.f : Code<BK>::c0 * 0.5f;
   const float ksc = (BK == 1 ? 0.5f : 2.f) * a.qscale;
 
-  float m = kNoScore, l = 0.f, zterm = 0.f;
+  float m = kNoScore, most = kNoScore, l = 0.f, zterm = 0.f;  // the row's reference, the lane's maximum
   bool zraw = false;  // the value zeros enter lifted while they are small
   const _Float16 sf = (_Float16)ldexpf(1.f, min(X + Code<BV>::reach, 13));  // scales lifted like the operands
   const h2_t sfac = {sf, sf};
@@ -234,6 +234,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
       for (int e = 0; e < 8; ++e) s[e] = 16 * (e >> 2) + (e & 3) < left ? s[e] : kNoScore;
     }
     float top = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+    most = fmaxf(most, top);
     if (__builtin_amdgcn_ballot_w64(top - m > kTop)) {
       // the row's maximum over its four lanes; rows above the limit move
       // their reference
@@ -312,6 +313,9 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
+  most = fmaxf(most, __shfl_xor(most, 16));
+  most = fmaxf(most, __shfl_xor(most, 32));
+  const float to_max = __builtin_amdgcn_exp2f(m - most);  // records are relative to the maximum
   // zero-point terms of group 4blk + r, row col, to the lanes of its channels
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -326,11 +330,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int g = (FINE ? 16 * t + 4 * blk + r : 16 * t) >> gvsh;
-      acc[t][r] = fmaf(acc[t][r], unit, fmaf(Code<BV>::c0, zsh[wv][1][g][col], zsh[wv][0][g][col]));
+      acc[t][r] = fmaf(acc[t][r], unit, fmaf(Code<BV>::c0, zsh[wv][1][g][col], zsh[wv][0][g][col])) * to_max;
     }
   TailState<1> st;
-  st.m[0] = l > 0.f ? m : -__builtin_inff();
-  st.l[0] = l;
+  st.m[0] = l > 0.f ? most : -__builtin_inff();
+  st.l[0] = l * to_max;
 #pragma unroll
   for (int t = 0; t < 8; ++t) st.acc[0][t] = acc[t];
   for (int r0 = 0; r0 < rows; r0 += kPartRows) {

@@ -157,6 +157,15 @@ __device__ __forceinline__ void add_raw(u4_t w, const h8_t (&ph)[N], const h8_t 
   }
 }
 
+// acc plus the two halves of w.  The softmax's denominator adds what the
+// products add, the weights' hi and lo halves: a rounding that the weights
+// share then leaves the quotient.
+__device__ __forceinline__ float add_halves(uint32_t w, float acc) {
+  asm("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel_hi:[1,0,0]" : "+v"(acc) : "v"(w));
+  asm("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(acc) : "v"(w));
+  return acc;
+}
+
 // Buffer resource over one (sequence, kv head) block.  Every load is
 // base + per-lane offset + uniform offset: the per-block part is scalar
 // arithmetic and the vector ALU does no address math.  The host keeps the

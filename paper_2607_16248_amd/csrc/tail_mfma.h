@@ -7,8 +7,9 @@
 // 32-token block in the lanes that are the B operand of O^T = V^T P^T.  The
 // keys' rows are operands as they lie in memory; an operand of V^T gathers 8
 // tokens of one channel, 16 channels (32 bytes) per row.  q, k and v are exact
-// fp16 operands; p enters as hi + lo halves (22 bits), scaled to at most 2^14
-// so that both stay normal numbers.
+// fp16 operands; p = 2^(score - maximum) enters as hi + lo halves (22 bits),
+// times 2^14 so that both stay normal numbers (a reference 14 below the maximum
+// would round the difference to 2^-21 instead).  Records hold the maximum.
 //
 // What bounds it: latency.  A wave's first block is four dependent steps
 // (arguments, the rows, two products, the reduction), and four waves share
@@ -30,7 +31,9 @@ using mfma_ops::h2_t;
 using mfma_ops::h8_t;
 using mfma_ops::u4_t;
 
-// row 16u + col of the tile in lane (col, block): reference, its weights' sum
+constexpr float kTailUnit = 16384.f;  // weights times 2^14 inside tail_split
+
+// row 16u + col of the tile in lane (col, block): maximum, its weights' sum
 // over the lane's tokens, accumulators of channels 16t + 4 * block + r
 template <int NT>
 struct TailState {
@@ -133,8 +136,8 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
       }
       top = fmaxf(top, __shfl_xor(top, 16));
       top = fmaxf(top, __shfl_xor(top, 32));
-      // weights reach 2^14; a row with no visible token yet keeps m = -inf
-      const float mn = fmaxf(st.m[u], top - 14.f);
+      // a row with no visible token yet keeps m = -inf
+      const float mn = fmaxf(st.m[u], top);
       const bool none = mn == -__builtin_inff();
       const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(st.m[u] - mn);
       st.m[u] = mn;
@@ -144,12 +147,12 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
       u4_t hw, lw;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const float p0 = none ? 0.f : __builtin_amdgcn_exp2f(s[2 * t] - mn);
-        const float p1 = none ? 0.f : __builtin_amdgcn_exp2f(s[2 * t + 1] - mn);
-        st.l[u] += p0 + p1;
+        const float p0 = none ? 0.f : __builtin_amdgcn_exp2f(s[2 * t] - mn) * kTailUnit;
+        const float p1 = none ? 0.f : __builtin_amdgcn_exp2f(s[2 * t + 1] - mn) * kTailUnit;
         const h2_t hi = {(_Float16)p0, (_Float16)p1};
         hw[t] = mfma_ops::h2u(hi);
         lw[t] = mfma_ops::h2u((h2_t){(_Float16)(p0 - (float)hi.x), (_Float16)(p1 - (float)hi.y)});
+        st.l[u] = mfma_ops::add_halves(lw[t], mfma_ops::add_halves(hw[t], st.l[u]));
       }
       ph[u] = __builtin_bit_cast(h8_t, hw);
       pl[u] = __builtin_bit_cast(h8_t, lw);
@@ -175,7 +178,8 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) st.acc[u][t] *= raw[t] ? 1.f : 1.f / mfma_ops::kLift;
+    for (int t = 0; t < 8; ++t) st.acc[u][t] *= raw[t] ? 1.f / kTailUnit : 1.f / kTailUnit / mfma_ops::kLift;
+    st.l[u] *= 1.f / kTailUnit;
     st.l[u] += __shfl_xor(st.l[u], 16);
     st.l[u] += __shfl_xor(st.l[u], 32);
   }

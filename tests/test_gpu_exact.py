@@ -112,3 +112,32 @@ def test_head_past_4gib():
     err = ((out - ref).abs().amax(1) / size.amax(1)).max().item()
     log(f"[exact] {n} tokens of a head past 4 GiB: {err:.2e}")
     assert err <= TOL
+
+
+@pytest.mark.parametrize("gq,bk,bv,gv", [(4, 4, 2, 32), (8, 2, 2, 16), (5, 1, 8, 64), (4, 2, 2, 32), (8, 4, 4, 32), (1, 1, 1, 64)])
+def test_records_hold_the_split_maximum(gq, bk, bv, gv):
+    """kvq_decode_partials: [0] is the split's largest base-2 score, [1] and [4..] are relative to it, in every split of
+    the mixed and fine-grouped classes and in the fp16 tail's split of every class.  A score's error is 2^-24 of the
+    sum of its terms' magnitudes per addition (up to 2^7 of them, half the bits random): 2^-20 of it."""
+    w, st = W(gq, (1000,), bk, bv, 32, gv, 100), 256
+    c = Case(w)
+    c.append_all()
+    kvq.kvq_set_split_tokens(c.cache.handle, st)
+    ws = torch.full((kvq.kvq_workspace_bytes(c.cache.handle) // 4,), float("nan"), device="cuda")
+    kvq.kvq_decode_partials(c.cache.handle, c.qd, ws)
+    kd, vd = (x.double().cpu().numpy() for x in c.cache.dequant(0, 0, 1000))
+    lq, rows = 896, 2 * gq
+    splits = [(t, min(t + st, lq)) for t in range(0, lq, st)] + [(lq, 1000)]
+    rec = ws.cpu().numpy()[:len(splits) * rows * 132].reshape(len(splits), rows, 132).astype(np.float64)
+    exact = (bk <= 2) != (bv <= 2) or gv < 32
+    for i, (t0, t1) in enumerate(splits):
+        if not exact and i < len(splits) - 1:
+            continue
+        for r in range(rows):
+            k, v, q = kd[t0:t1, r // gq], vd[t0:t1, r // gq], c.q[0][r].astype(np.float64)
+            s = k @ q * (np.log2(np.e) / 128 ** 0.5)
+            slack = 2.0 ** -20 * (np.abs(k) @ np.abs(q)).max() * (np.log2(np.e) / 128 ** 0.5)
+            assert abs(rec[i, r, 0] - s.max()) <= slack, (i, r)
+            p = np.exp2(s - s.max())
+            assert abs(rec[i, r, 1] - p.sum()) <= (2.0 ** -18 + slack) * p.sum(), (i, r)
+            assert np.abs(rec[i, r, 4:] - p @ v).max() <= (2.0 ** -17 + slack) * (p @ np.abs(v)).max(), (i, r)
