@@ -23,6 +23,8 @@
 // 16 K1V4 47 (187); error against 64 bits 7e-7 (1.3e-6).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "decode_common.h"
 #include "kvq_internal.h"
 #include "kvq_layout.h"
@@ -47,6 +49,7 @@ template <int BK, int BV>
 struct ExactBlock {
   uint32_t kx[2][BK], vx[2 * BV];
   u4_t ks[4], kz[4];
+  uint32_t cs, cz;  // the lane's two of the key group's 128 scales and zeros
 };
 // Its value meta; with FINE groups loaded at the block's start instead of a
 // block ahead (32 registers more).
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
   for (int n = 0; n < (FINE ? 8 : 4); ++n) vgl[n] = ((FINE ? 16 * n + col : 32 * n) / a.gv) * 64 + 16 * blk;
   const int zrow = col < ng ? col : 0;
-  auto load = [&](int i, ExactBlock<BK, BV>& o) {
+  auto load = [&](auto lift_c, int i, ExactBlock<BK, BV>& o) {
     int t;
     const uint8_t* seg = a.arena + packed_seg(a.pm, S.head0, a.head_stride, S.seq, wk.h, token_of(i), t);
     const uint8_t* kr = seg + region(a.kc) + (size_t)t * 16 * BK + col * 16 * BK + blk * 4 * BK;
@@ -158,6 +161,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     for (int kb = 0; kb < 4; ++kb) {
       o.ks[kb] = *reinterpret_cast<const u4_t*>(km + 64 * kb);
       o.kz[kb] = *reinterpret_cast<const u4_t*>(km + 256 + 64 * kb);
+    }
+    const uint32_t* kmw = reinterpret_cast<const uint32_t*>(seg + region(a.km) + (size_t)(t >> gsh) * 512);
+    if constexpr (decltype(lift_c)::value) {
+      o.cs = kmw[lane];
+      o.cz = kmw[64 + lane];
     }
     const uint8_t* vr = seg + region(a.vc) + (size_t)(t >> 5) * 512 * BV + lane * 8 * BV;
     if constexpr (BV == 1) {
@@ -189,6 +197,22 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   constexpr float kAlpha = BK == 1 ? -2.f : 0.5f, kBeta = BK == 1 ? -1.f : Code<BK>::c0 * 0.5f;
   const float ksc = (BK == 1 ? 0.5f : 2.f) * a.qscale;
 
+  // Small key numbers lose bits: halves below 2^-14 in the products, scales below
+  // 2^-13 already in their half and in the lo parts, about 2^-25 of the query for
+  // each.  Under queries of 8 or more they enter lifted by 2^12, in products of
+  // their own next to larger ones (under smaller queries they move a weight by
+  // less than 3e-7): keys of 2^-18 under queries of 2^14 are off by 5e-4 without
+  // it and 1e-6 with it.  The test and the lift's registers cost a loop with a
+  // block in flight 2 to 17%, so such queries take a loop of their own without
+  // one (2 to 8% slower).  Classes whose loop with a block in flight spills go
+  // without for every query: 32768 tokens, groups of 16 channels, K8V8 23 us
+  // (32), K4V8 23 (27).
+  constexpr bool kAhead = BK + BV < 10 || BK == 2;
+  constexpr uint32_t kTinyScale = 0x0800u;  // 2^-13
+  auto any_half = [](uint32_t w, uint32_t from, uint32_t to) -> bool {  // of the wave's, in [from, to)
+    return __builtin_amdgcn_ballot_w64((w & 0xFFFFu) - from < to - from || (w >> 16) - from < to - from) != 0;
+  };
+
   float m = kNoScore, most = kNoScore, l = 0.f, zterm = 0.f;  // the row's reference, the lane's maximum
   bool zraw = false;  // the value zeros enter lifted while they are small
   const _Float16 sf = (_Float16)ldexpf(1.f, min(X + Code<BV>::reach, 13));  // scales lifted like the operands
@@ -197,38 +221,90 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
   for (int t = 0; t < 8; ++t) acc[t] = (f4_t){0.f, 0.f, 0.f, 0.f};
 
-  auto process = [&](const ExactBlock<BK, BV>& cur, ValueMeta<FINE>& vm, int i) {
+  auto process = [&](auto lift_c, const ExactBlock<BK, BV>& cur, ValueMeta<FINE>& vm, int i) {
     if constexpr (FINE) load_meta(i, vm);
-    if ((i & ((1 << bsh) - 1)) == 0) {  // the key group's zero-point term, the same in every lane of the row
-      f4_t tz = {0.f, 0.f, 0.f, 0.f}, ts = {0.f, 0.f, 0.f, 0.f};
+    constexpr bool LIFT = decltype(lift_c)::value;
+    const bool first = (i & ((1 << bsh) - 1)) == 0;  // of its key group
+    // raw scores of the scales ks (the group's, or a part of them; the rest 0)
+    auto raw_scores = [&](const u4_t (&ks)[4], f4_t (&d)[2]) {
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        tz = mfma(__builtin_bit_cast(h8_t, cur.kz[kb]), __builtin_bit_cast(h8_t, q[kb]), tz);
-        ts = mfma(__builtin_bit_cast(h8_t, cur.ks[kb]), __builtin_bit_cast(h8_t, q[kb]), ts);
+      for (int mb = 0; mb < 2; ++mb) {
+        d[mb] = (f4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+          uint32_t x[2];
+          x[0] = cur.kx[mb][BK == 1 ? 0 : BK == 2 ? kb >> 1 : BK == 4 ? kb : 2 * kb];
+          x[1] = BK == 8 ? cur.kx[mb][2 * kb + 1 < BK ? 2 * kb + 1 : 0] : 0u;
+          u4_t hi, lo;
+          unpack_scaled<BK, false>(x, ks[kb], BK == 1 ? 4 * kb : 8 * (kb & 1), kfac, hi, lo);
+          d[mb] = mfma(__builtin_bit_cast(h8_t, hi), __builtin_bit_cast(h8_t, q[kb]), d[mb]);
+          if constexpr (Code<BK>::parts == 2)
+            d[mb] = mfma(__builtin_bit_cast(h8_t, lo), __builtin_bit_cast(h8_t, q[kb]), d[mb]);
+        }
       }
-      zterm = fmaf(kAlpha, tz[0], kBeta * ts[0]) * ksc;
-    }
-    f4_t d[2];
+    };
+    auto q_sum = [&](const u4_t (&x)[4]) {  // sum over the channels of q x, the same in every lane of the row
+      f4_t t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      d[mb] = (f4_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        uint32_t x[2];
-        x[0] = cur.kx[mb][BK == 1 ? 0 : BK == 2 ? kb >> 1 : BK == 4 ? kb : 2 * kb];
-        x[1] = BK == 8 ? cur.kx[mb][2 * kb + 1 < BK ? 2 * kb + 1 : 0] : 0u;
-        u4_t hi, lo;
-        unpack_scaled<BK, false>(x, cur.ks[kb], BK == 1 ? 4 * kb : 8 * (kb & 1), kfac, hi, lo);
-        d[mb] = mfma(__builtin_bit_cast(h8_t, hi), __builtin_bit_cast(h8_t, q[kb]), d[mb]);
-        if constexpr (Code<BK>::parts == 2)
-          d[mb] = mfma(__builtin_bit_cast(h8_t, lo), __builtin_bit_cast(h8_t, q[kb]), d[mb]);
-      }
-    }
+      for (int kb = 0; kb < 4; ++kb) t = mfma(__builtin_bit_cast(h8_t, x[kb]), __builtin_bit_cast(h8_t, q[kb]), t);
+      return t[0];
+    };
     const int tok = token_of(i), left = lim - tok - 4 * blk;  // token 16mb + 4blk + r is visible below it
     const bool masked = tok + 32 > first_limit;
     float s[8];
+    if (LIFT && (any_half(cur.cs, 1u, kTinyScale) || any_half(cur.cz & 0x7FFF7FFFu, 1u, 0x0400u))) {
+      // the small numbers lifted, apart from the others
+      u4_t part[4], rest[4];
+      if (first) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] = fmaf(d[e >> 2][e & 3], ksc, zterm);
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            uint32_t x, y;
+            split_subnormal(cur.kz[kb][n], x, y);
+            part[kb][n] = x;
+            rest[kb][n] = y;
+          }
+        zterm = kAlpha * ksc * fmaf(1.f / kLift, q_sum(rest), q_sum(part));
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] = 0.f;
+      f4_t d[2];
+      auto add = [&](float f) {
+        raw_scores(part, d);
+        if (first) zterm = fmaf(kBeta * f, q_sum(part), zterm);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] = fmaf(d[e >> 2][e & 3], f, s[e]);
+      };
+      auto keep = [&](bool small) {
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+          for (int n = 0; n < 4; ++n) {
+            const uint32_t w = cur.ks[kb][n];
+            const uint32_t lo = ((w & 0xFFFFu) < kTinyScale) == small ? 0xFFFFu : 0u, hi = ((w >> 16) < kTinyScale) == small ? 0xFFFF0000u : 0u;
+            part[kb][n] = w & (lo | hi);
+          }
+      };
+      if (any_half(cur.cs, kTinyScale, 0x7FFFu)) {
+        keep(false);
+        add(ksc);
+      }
+      if (any_half(cur.cs, 1u, kTinyScale)) {
+        keep(true);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) part[kb] = __builtin_bit_cast(u4_t, lifted(part[kb], false));
+        add(ksc * (1.f / kLift));
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] += zterm;
+    } else {
+      if (first) zterm = fmaf(kAlpha, q_sum(cur.kz), kBeta * q_sum(cur.ks)) * ksc;
+      f4_t d[2];
+      raw_scores(cur.ks, d);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] = fmaf(d[e >> 2][e & 3], ksc, zterm);
+    }
     if (masked) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) s[e] = 16 * (e >> 2) + (e & 3) < left ? s[e] : kNoScore;
@@ -292,23 +368,39 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     }
   };
 
-  if (nblocks > 0) {
+  auto run = [&](auto lift_c) {
     const int last = nblocks - 1;
     ExactBlock<BK, BV> b0, b1;
     ValueMeta<FINE> m0, m1;
     auto fetch = [&](int i, ExactBlock<BK, BV>& o, ValueMeta<FINE>& vm) {
-      load(i, o);
+      load(lift_c, i, o);
       if constexpr (!FINE) load_meta(i, vm);
     };
+    if constexpr (decltype(lift_c)::value || !kAhead) {
+      for (int i = 0; i < nblocks; ++i) {
+        fetch(i, b0, m0);
+        process(lift_c, b0, m0, i);
+      }
+      return;
+    }
     fetch(0, b0, m0);
     int i = 0;
     for (; i + 2 <= nblocks; i += 2) {
       fetch(min(i + 1, last), b1, m1);
-      process(b0, m0, i);
+      process(lift_c, b0, m0, i);
       fetch(min(i + 2, last), b0, m0);
-      process(b1, m1, i + 1);
+      process(lift_c, b1, m1, i + 1);
     }
-    if (i < nblocks) process(b0, m0, i);
+    if (i < nblocks) process(lift_c, b0, m0, i);
+  };
+  if (nblocks > 0) {
+    uint32_t qtop = 0u;  // the tile's largest |q| (the lanes hold all of it)
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) qtop = max(qtop, max(q[kb][n] & 0x7FFFu, (q[kb][n] >> 16) & 0x7FFFu));
+    if (__builtin_amdgcn_ballot_w64(qtop >= 0x4800u) != 0) run(std::true_type{});  // 8.0
+    else run(std::false_type{});
   }
 
   l += __shfl_xor(l, 16);

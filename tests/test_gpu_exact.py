@@ -141,3 +141,24 @@ def test_records_hold_the_split_maximum(gq, bk, bv, gv):
             p = np.exp2(s - s.max())
             assert abs(rec[i, r, 1] - p.sum()) <= (2.0 ** -18 + slack) * p.sum(), (i, r)
             assert np.abs(rec[i, r, 4:] - p @ v).max() <= (2.0 ** -17 + slack) * (p @ np.abs(v)).max(), (i, r)
+
+
+@pytest.mark.parametrize("gq,bk,bv,gv,gk", [(4, 4, 2, 32, 32), (8, 8, 1, 32, 64), (5, 2, 8, 64, 32), (4, 8, 8, 16, 128), (2, 1, 4, 32, 32),
+                                            (1, 2, 2, 8, 32), (4, 8, 4, 8, 32)])
+@pytest.mark.parametrize("ks,qs,outlier", [(2.0 ** -8, 2.0 ** 8, 0), (2.0 ** -12, 2.0 ** 12, 0), (2.0 ** -18, 2.0 ** 14, 0),
+                                           (2.0 ** -18, 2.0 ** 14, 1), (2.0 ** -18, 7.0, 0)])
+def test_small_keys(gq, bk, bv, gv, gk, ks, qs, outlier):
+    """Keys down to subnormal fp16 under queries that bring their scores back, alone and with a channel too large to be
+    lifted (then the scores' own sums carry its rounding: 2^-24 of 8192 * 0.5 times log2(e) / sqrt(128), twice)."""
+    w = W(gq, (700,), bk, bv, gk, gv, 40)
+    c = Case(w)
+    c.K[0] = (c.K[0].astype(np.float32) * ks).astype(np.float16)
+    c.q[0] = np.clip(c.q[0].astype(np.float32) * qs, -60000, 60000).astype(np.float16)
+    if outlier:
+        c.K[0][:, :, 5] = np.where(np.arange(700) % 2 == 0, 8192, -8192).astype(np.float16)[:, None]
+        c.q[0][:, 5] = np.float16(2.0 ** -12)
+    c.qd = torch.from_numpy(np.stack(c.q)).cuda()
+    c.append_all()
+    err = row_rel_err(c.decode()[0], c.oracle_out(0)).max()
+    log(f"[exact] {w.name} keys {ks:g} queries {qs:g} outlier {outlier}: {err:.2e}")
+    assert err <= TOL
