@@ -167,12 +167,21 @@ __device__ __forceinline__ void tail_split(const DecodeArgs& a, const DecodeSeq&
 #pragma unroll
         for (int u = 0; u < NT; ++u) st.acc[u][t] *= 1.f / mfma_ops::kLift;
       }
-      const h8_t v8 = mfma_ops::lifted(w, raw[t]);
+      f4_t x[NT];
 #pragma unroll
-      for (int u = 0; u < NT; ++u) {
-        st.acc[u][t] = mfma_ops::mfma(v8, ph[u], st.acc[u][t]);
-        st.acc[u][t] = mfma_ops::mfma(v8, pl[u], st.acc[u][t]);
+      for (int u = 0; u < NT; ++u) x[u] = st.acc[u][t];
+      if (raw[t]) {  // (rows that see no large value keep the bits of their small ones)
+        mfma_ops::add_raw<NT>(w, ph, pl, x);
+      } else {
+        const h8_t v8 = mfma_ops::lifted(w, false);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          x[u] = mfma_ops::mfma(v8, ph[u], x[u]);
+          x[u] = mfma_ops::mfma(v8, pl[u], x[u]);
+        }
       }
+#pragma unroll
+      for (int u = 0; u < NT; ++u) st.acc[u][t] = x[u];
     }
   }
 #pragma unroll

@@ -83,3 +83,21 @@ def test_value_ranges(gq, bits, scale, big):
     err = row_rel_err(c.decode()[0], c.oracle_out(0)).max()
     log(f"[tail] {c.w.name} scale {scale:g} big {big}: {err:.2e}")
     assert err <= 2.0 ** -20 * 4
+
+
+@pytest.mark.parametrize("gq,bits,n_q", [(1, (2, 2), 40), (4, (1, 1), 16), (8, (8, 8), 8), (2, (4, 1), 30)])
+@pytest.mark.parametrize("big", [90, 130, 147])
+def test_rows_that_see_only_small_values(gq, bits, n_q, big):
+    """Subnormal values and one large token: the queries before it see subnormal ones alone.  A row that the large token
+    carries has its score's error (base 2, magnitude up to 2^6) as its own: 2^-17, as with many rows."""
+    c = Case(W(150, gq, bits[0], bits[1], 150))
+    c.V[0] = (c.V[0].astype(np.float32) * 2.0 ** -20).astype(np.float16)
+    c.V[0][big] = (c.V[0][big].astype(np.float32) * 2.0 ** 26).astype(np.float16)
+    c.append_all()
+    q = gen_q_chunk(c.w, n_q)
+    out = c.cache.chunk(torch.from_numpy(q[None]).cuda())[0].cpu().numpy()
+    err = row_rel_err(out, oracle.chunk_seq(q, c.K[0], c.V[0], bits[0], bits[1], 32, 32, 150))
+    before = max(0, big - (150 - n_q))  # queries that don't see it
+    log(f"[tail] {c.w.name} n_q {n_q} big {big}: {err[:before].max() if before else 0:.2e} {err[before:].max():.2e}")
+    assert before == 0 or err[:before].max() <= 2.0 ** -18
+    assert err[before:].max() <= 2.0 ** -17
