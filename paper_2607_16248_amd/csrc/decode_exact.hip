@@ -7,20 +7,23 @@
 // (scaled_ops.h), weights p as hi + lo halves.  The products are transposed,
 //   S^T = K' Q^T   (16 tokens x 16 rows; a lane holds 8 of its row's weights)
 //   O^T = V'^T P^T (the same lanes' weights are the B operand),
-// so a wave needs no LDS between them; zero-points enter as one more product
-// each: K' Q^T with the group's z (and s) in every row gives sum_c q z in
-// every lane, and [z], [s] of the value groups times P^T the value terms.
+// so a wave needs no LDS between them; zero-points enter as products of their
+// own: K' Q^T with the group's z (and s) in every row gives sum_c q z in
+// every lane, and z + c0 s of the value groups, in hi + lo halves, times P^T
+// the value terms (z and s apart are opposite and leave their rounding where
+// the values average out: 1e-6 over 512 tokens of equal weight, 2e-7 so).
 //
 // What bounds it: the vector unit, by the unpacking: 2 to 6 instructions per
 // operand dword, 64 or more dwords per 32-token block, against 40 to 60
 // products.  Each wave takes blocks of its own (key groups j0 + wave + 4n of
-// the split), the next block's loads in flight; two waves per SIMD.  The
-// vector kernel it replaces multiplied each code by each row's query (64 *
+// the split), the next block's loads in flight but for the 8-bit classes; two
+// waves per SIMD, no spills but K8V8's with groups of 8 or 16 (10 registers).
+// The vector kernel it replaces multiplied each code by each row's query (64 *
 // rows multiply-adds per token half) from LDS.  Measured, 8 kv heads, split
 // kernel alone: 32768 tokens, four heads each, K4V2 16.9 us (vector 29.8),
 // K8V1 17.9 (30.5), K2V2 with groups of 16 channels 16.8 (29.3); four sequences
 // of that length with five heads K4V2 47 (122), with eight heads and groups of
-// 16 K1V4 47 (187); error against 64 bits 7e-7 (1.3e-6).
+// 16 K1V4 47 (187); error against 64 bits 2e-7 to 9e-7 (3e-7 to 1e-6).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -61,7 +64,7 @@ struct ValueMeta {
 template <int BK, int BV, bool FINE>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_exact_kernel(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) Reduce<kPartRows> red;
-  __shared__ float zsh[kWaves][2][16][17];  // value zero-point terms: [z, s][group][row]
+  __shared__ float zsh[kWaves][16][17];  // value zero-point terms: [group][row]
   const Work wk = find_work<true>(a);
   const DecodeSeq& S = a.seq[wk.si];
   const uint8_t* ring = a.arena + S.head0 + (uint64_t)wk.h * a.head_stride;
@@ -214,10 +217,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   };
 
   float m = kNoScore, most = kNoScore, l = 0.f, zterm = 0.f;  // the row's reference, the lane's maximum
-  bool zraw = false;  // the value zeros enter lifted while they are small
-  const _Float16 sf = (_Float16)ldexpf(1.f, min(X + Code<BV>::reach, 13));  // scales lifted like the operands
-  const h2_t sfac = {sf, sf};
-  f4_t acc[8], zaz = {0.f, 0.f, 0.f, 0.f}, zas = {0.f, 0.f, 0.f, 0.f};
+  f4_t acc[8], zal = {0.f, 0.f, 0.f, 0.f}, zar = {0.f, 0.f, 0.f, 0.f};  // value zero-point terms: lifted, as they are
 #pragma unroll
   for (int t = 0; t < 8; ++t) acc[t] = (f4_t){0.f, 0.f, 0.f, 0.f};
 
@@ -322,8 +322,8 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
       l *= alpha;
 #pragma unroll
       for (int t = 0; t < 8; ++t) acc[t] *= alpha;
-      zaz *= alpha;
-      zas *= alpha;
+      zal *= alpha;
+      zar *= alpha;
     }
     u4_t hw, lw;
 #pragma unroll
@@ -339,19 +339,43 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
       lw[t] = h2u((h2_t){(_Float16)(p0 - (float)hi.x), (_Float16)(p1 - (float)hi.y)});
     }
     const h8_t ph = __builtin_bit_cast(h8_t, hw), pl = __builtin_bit_cast(h8_t, lw);
-    if (!zraw && needs_raw(vm.zz)) {
-      zraw = true;
-      zaz *= 1.f / kLift;
-    }
-    const h8_t z8 = lifted(vm.zz, zraw);
-    u4_t sw;
+    // z + c0 s of the value groups, in hi + lo halves (22 bits): lifted below 8,
+    // as it is in an accumulator of its own from there on
+    auto add_mid = [&](const float (&x)[8], f4_t& sum) {
+      u4_t hi, lo;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) sw[t] = h2u(u2h(vm.zs[t]) * sfac);
-    const h8_t s8 = __builtin_bit_cast(h8_t, sw);
-    zaz = mfma(z8, ph, zaz);
-    zas = mfma(s8, ph, zas);
-    zaz = mfma(z8, pl, zaz);
-    zas = mfma(s8, pl, zas);
+      for (int t = 0; t < 4; ++t) {
+        const h2_t h = {(_Float16)x[2 * t], (_Float16)x[2 * t + 1]};
+        hi[t] = h2u(h);
+        lo[t] = h2u((h2_t){(_Float16)(x[2 * t] - (float)h.x), (_Float16)(x[2 * t + 1] - (float)h.y)});
+      }
+      sum = mfma(__builtin_bit_cast(h8_t, hi), ph, sum);
+      sum = mfma(__builtin_bit_cast(h8_t, hi), pl, sum);
+      sum = mfma(__builtin_bit_cast(h8_t, lo), ph, sum);
+    };
+    float mid[8], mtop = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const h2_t z = u2h(vm.zz[t]) * (h2_t){(_Float16)kLift, (_Float16)kLift}, sc = u2h(vm.zs[t]);
+      mid[2 * t] = fmaf((float)sc.x, Code<BV>::c0 * kLift, (float)z.x);
+      mid[2 * t + 1] = fmaf((float)sc.y, Code<BV>::c0 * kLift, (float)z.y);
+      mtop = fmaxf(mtop, fmaxf(fabsf(mid[2 * t]), fabsf(mid[2 * t + 1])));
+    }
+    if (__builtin_amdgcn_ballot_w64(!(mtop < 8.f * kLift)) == 0) {
+      add_mid(mid, zal);
+    } else {
+      float big[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const h2_t z = u2h(vm.zz[e >> 1]), sc = u2h(vm.zs[e >> 1]);
+        const float x = fmaf((float)(e & 1 ? sc.y : sc.x), Code<BV>::c0, (float)(e & 1 ? z.y : z.x));
+        const bool is_big = fabsf(x) >= 8.f;
+        big[e] = is_big ? x : 0.f;
+        mid[e] = is_big ? 0.f : x * kLift;
+      }
+      add_mid(mid, zal);
+      add_mid(big, zar);
+    }
 #pragma unroll
     for (int mb = 0; mb < 8; ++mb) {
       uint32_t x[2];
@@ -411,8 +435,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   // zero-point terms of group 4blk + r, row col, to the lanes of its channels
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    zsh[wv][0][4 * blk + r][col] = zraw ? zaz[r] : zaz[r] * (1.f / kLift);
-    zsh[wv][1][4 * blk + r][col] = zas[r] * (1.f / (float)sf);
+    zsh[wv][4 * blk + r][col] = fmaf(zal[r], 1.f / kLift, zar[r]);
   }
   wave_lds_sync();
   const float unit = Code<BV>::unit * ldexpf(1.f, -X);
@@ -422,7 +445,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int g = (FINE ? 16 * t + 4 * blk + r : 16 * t) >> gvsh;
-      acc[t][r] = fmaf(acc[t][r], unit, fmaf(Code<BV>::c0, zsh[wv][1][g][col], zsh[wv][0][g][col])) * to_max;
+      acc[t][r] = fmaf(acc[t][r], unit, zsh[wv][g][col]) * to_max;
     }
   TailState<1> st;
   st.m[0] = l > 0.f ? most : -__builtin_inff();

@@ -162,3 +162,16 @@ def test_small_keys(gq, bk, bv, gv, gk, ks, qs, outlier):
     err = row_rel_err(c.decode()[0], c.oracle_out(0)).max()
     log(f"[exact] {w.name} keys {ks:g} queries {qs:g} outlier {outlier}: {err:.2e}")
     assert err <= TOL
+
+
+@pytest.mark.parametrize("bk,bv,gv", [(1, 4, 32), (2, 8, 32), (4, 2, 32), (1, 1, 16), (8, 8, 16)])
+def test_equal_weights(bk, bv, gv):
+    """All scores near zero: values average out to 1/20 of their size, and their zero-points must not leave a rounding
+    of their own size.  Values in 22 bits: 2^-22 of up to 2^2 each, averaged over 2^9 tokens, against outputs of 2^-3."""
+    c = Case(W(4, (512,), bk, bv, 32, gv))
+    c.q[0] = (c.q[0].astype(np.float32) * 2.0 ** -10).astype(np.float16)
+    c.qd = torch.from_numpy(np.stack(c.q)).cuda()
+    c.append_all()
+    err = row_rel_err(c.decode()[0], c.oracle_out(0)).max()
+    log(f"[exact] {c.w.name} equal weights: {err:.2e}")
+    assert err <= 2.0 ** -20
