@@ -576,7 +576,7 @@ Rows rows_for(const kvq_cache* c, bool matrix, int nqry, int bk, int bv) {
 
 struct SplitPlan {
   std::vector<int32_t> st, nq, ns, base;  // per sequence: split length, packed splits, all splits, first record
-  std::vector<uint8_t> direct;            // per sequence: written by the split launch, not merged
+  std::vector<uint8_t> direct;            // per sequence: written by the split launch, not merged (empty: none)
   int64_t records = 0;   // what the launches write
   int64_t required = 0;  // what the caller's workspace has to hold
   int nqry = 1;
@@ -664,7 +664,6 @@ SplitPlan plan_splits(const kvq_cache* c, int nqry = 1, size_t ws_bytes = 0) {
   p.nq.resize(B);
   p.ns.resize(B);
   p.base.resize(B);
-  p.direct.assign(B, 0);
   for (int i = 0; i < B; ++i) {
     p.nq[i] = (c->Lq[i] + p.st[i] - 1) / p.st[i];
     p.ns[i] = p.nq[i] + (c->L[i] > c->Lq[i] ? 1 : 0);
@@ -672,9 +671,11 @@ SplitPlan plan_splits(const kvq_cache* c, int nqry = 1, size_t ws_bytes = 0) {
     p.records += p.ns[i];
   }
   p.required = p.records;
+  if (nqry <= 1) return p;
   bool many = false;
   for (auto& cl : classes) many |= many_rows(c, cl.second[0], nqry);
   if (!many) return p;
+  p.direct.assign(B, 0);
   // re-plan the many-row classes; the records of the others come first
   int64_t left = (int64_t)(ws_bytes / ((size_t)c->d.num_q_heads * nqry * kvq::kRecFloats * sizeof(float)));
   p.records = 0;
@@ -784,7 +785,7 @@ kvq_status run_merge(const kvq_cache* c, const SplitPlan& p, const void* ws, flo
     m.hq = d.num_q_heads * p.nqry;  // out [batch][nqry][Hq] = [batch][nqry * Hq]
     int n = 0;
     for (int i = b; i < std::min(d.batch, b + kvq::kMaxSeqPerLaunch); ++i) {
-      if (p.direct[i]) continue;
+      if (!p.direct.empty() && p.direct[i]) continue;
       m.seq[n].seq = i; m.seq[n].nsplit = p.ns[i]; m.seq[n].ws_base = p.base[i];
       ++n;
     }
