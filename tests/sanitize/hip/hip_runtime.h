@@ -2,7 +2,8 @@
  * host code uses, so that kvq_api.cpp can be compiled by the system C++
  * compiler with AddressSanitizer and UBSan and run without a GPU.
  * Test infrastructure only: "device" memory is host memory here, copies are
- * memcpy, and kernel launches do nothing (tests/sanitize/hip_stub.cpp). */
+ * memcpy, and kernel launches touch the ranges that the kernels would
+ * (tests/sanitize/hip_stub.cpp). */
 #pragma once
 #include <stddef.h>
 
@@ -22,5 +23,4 @@ hipError_t hipGetDevice(int* dev);
 hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t attr, int dev);
 const char* hipGetErrorString(hipError_t e);
 hipError_t hipMemcpy(void* dst, const void* src, size_t bytes, hipMemcpyKind kind);
-hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t s);
 hipError_t hipStreamSynchronize(hipStream_t s);

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <sanitizer/asan_interface.h>
 #include <sys/mman.h>
 #include <vector>
 
@@ -23,14 +24,19 @@ static int g_fail = 0;
     }                                                                   \
   } while (0)
 
-struct Buf {  // 256-byte aligned host buffer
+struct Buf {  // 256-byte aligned host buffer; what its last 256 bytes have past it is poisoned
   void* p = nullptr;
-  size_t n = 0;
-  explicit Buf(size_t bytes) : n(bytes) {
-    p = std::aligned_alloc(256, (bytes + 255) / 256 * 256 + 256);
-    std::memset(p, 0, (bytes + 255) / 256 * 256 + 256);
+  size_t n = 0, room = 0;
+  explicit Buf(size_t bytes) : n(bytes), room((bytes + 255) / 256 * 256 + (bytes == 0) * 256) {
+    p = std::aligned_alloc(256, room);
+    std::memset(p, 0, bytes);
+    ASAN_POISON_MEMORY_REGION(static_cast<char*>(p) + bytes, room - bytes);
   }
-  ~Buf() { std::free(p); }
+  ~Buf() {
+    ASAN_UNPOISON_MEMORY_REGION(p, room);
+    std::free(p);
+  }
+  Buf(const Buf&) = delete;
   template <class T> T* as() { return static_cast<T*>(p); }
 };
 
@@ -101,7 +107,7 @@ static void exercise(const kvq_cache_desc& d) {
       }
     }
     const size_t wsb = kvq_workspace_bytes(c);
-    Buf ws(wsb + 16);
+    Buf ws(wsb);
     EXPECT(kvq_decode_attention(c, q.p, out.as<float>(), ws.p, wsb, nullptr) == KVQ_OK);
     EXPECT(kvq_decode_attention(c, q.p, out.as<float>(), ws.p, 16, nullptr) == KVQ_ERR_CAPACITY);  // < one record
     EXPECT(kvq_decode_partials(c, q.p, ws.p, wsb, nullptr) == KVQ_OK);
@@ -112,15 +118,21 @@ static void exercise(const kvq_cache_desc& d) {
     for (int nq : {1, 2, 3, 5, 7, 13, 33, 64}) {
       if (nq > Lmin) continue;
       const size_t cw = kvq_chunk_workspace_bytes(c, nq);
-      Buf cws(cw + 16);
+      Buf cws(cw);
       EXPECT(kvq_chunk_attention(c, q.p, nq, out.as<float>(), cws.p, cw, nullptr) == KVQ_OK);
+      for (size_t w = cw / 2 / 16 * 16; nq == 64 && w > 0; w = w / 2 / 16 * 16) {  // down to the smallest that it takes
+        Buf less(w);
+        const kvq_status st = kvq_chunk_attention(c, q.p, nq, out.as<float>(), less.p, w, nullptr);
+        EXPECT(st == KVQ_OK || st == KVQ_ERR_CAPACITY);
+        if (st != KVQ_OK) break;
+      }
     }
     ++step;
   }
   for (int s = 0; s < B; ++s)
     for (int h = 0; h < H; ++h) {
       const size_t eb = kvq_export_bytes(c, s, h);
-      Buf img(eb + 1);
+      Buf img(eb);
       EXPECT(kvq_export(c, s, h, img.p, eb, nullptr) == KVQ_OK);
       if (eb > 0) EXPECT(kvq_export(c, s, h, img.p, eb - 1, nullptr) == KVQ_ERR_CAPACITY);
     }
@@ -132,7 +144,7 @@ static void exercise(const kvq_cache_desc& d) {
   EXPECT(kvq_set_split_tokens(c, d.key_group * 4) == KVQ_OK);
   {
     const size_t wsb = kvq_workspace_bytes(c);
-    Buf ws(wsb + 16);
+    Buf ws(wsb);
     EXPECT(kvq_decode_attention(c, q.p, out.as<float>(), ws.p, wsb, nullptr) == KVQ_OK);
   }
   EXPECT(kvq_set_split_tokens(c, d.key_group + 1) == KVQ_ERR_ARG);
@@ -198,9 +210,9 @@ int main() {
     kvq_cache* c = nullptr;
     EXPECT(kvq_cache_init(&c, nullptr, nullptr, 0) == KVQ_ERR_ARG);
   }
-  exercise(desc(3, 32, 8, 700, 32, 32, 0, b1, b1));            // matrix layout, four heads
+  exercise(desc(3, 32, 8, 700, 32, 32, 0, b1, b1));            // four heads
   exercise(desc(2, 40, 8, 500, 32, 32, 128, b2, b2));          // five heads, fp16 window
-  exercise(desc(4, 32, 8, 400, 64, 32, 40, mixk, mixv));       // mixed widths, canonical layouts
+  exercise(desc(4, 32, 8, 400, 64, 32, 40, mixk, mixv));       // mixed widths
   exercise(desc(2, 16, 8, 300, 32, 16, 0, b2, b1));            // two heads per kv head, small value groups
   exercise(desc(2, 64, 8, 600, 128, 64, 7, b4, b4));           // eight heads, key groups of 128
   exercise(desc(3, 32, 8, 900, 32, 32, 0, b8, b8, 64));        // paged
@@ -220,7 +232,7 @@ int main() {
     p.det_w1 = p.det_b1 = p.det_w2 = p.corr_w1 = p.corr_b1 = p.corr_w2 = w.data();
     std::vector<float> logits(2 * 1000, 0.f);
     const size_t wsb = dgap_workspace_bytes(2, 1000, 16);
-    Buf ws(wsb + 16);
+    Buf ws(wsb);
     EXPECT(dgap_restore(&p, logits.data(), 2, ws.p, wsb, nullptr, nullptr) == KVQ_OK);
     EXPECT(dgap_restore(&p, logits.data(), 2, ws.p, wsb - 1, nullptr, nullptr) != KVQ_OK);
     EXPECT(dgap_restore(nullptr, logits.data(), 2, ws.p, wsb, nullptr, nullptr) == KVQ_ERR_ARG);

@@ -4,9 +4,10 @@
   lengths, windows, ties, constant and subnormal groups, the range error.
 - The library's host code (paper_2607_16248_amd/csrc/kvq_api.cpp: argument
   checks, length bookkeeping, page lists, split plans, workspace sizes,
-  export offsets) with host buffers standing in for device memory and no-op
-  kernel launches (tests/sanitize/hip), so that every copy the host code
-  computes into the arena, the workspace or an export buffer is checked.
+  export offsets) with host buffers standing in for device memory and kernel
+  launches that touch the ranges their kernels would (tests/sanitize), so that
+  every offset the host code computes into the arena, the workspace, an input,
+  an output or an export buffer is checked.
 
 Both are built with the system compilers (gcc / g++), never for the GPU.
 """
