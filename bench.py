@@ -65,7 +65,8 @@ def matrix_path(w) -> bool:
 
 def source_digest() -> str:
     h = hashlib.sha256()
-    for f in ("csrc/merge.hip", "csrc/decode_mfma.hip", "csrc/chunk_mfma.hip", "csrc/mfma_common.h", "csrc/tail_mfma.h",
+    for f in ("csrc/merge.hip", "csrc/decode_mfma.hip", "csrc/decode_exact.hip", "csrc/chunk_mfma.hip",
+              "csrc/prefill_mfma.hip", "csrc/mfma_common.h", "csrc/scaled_ops.h", "csrc/tail_mfma.h",
               "csrc/decode_common.h", "csrc/kvq_internal.h", "csrc/kvq_layout.h", "build.py"):
         with open(os.path.join(ROOT, "paper_2607_16248_amd", f), "rb") as fh:
             h.update(fh.read())

@@ -227,7 +227,10 @@ size_t kvq_chunk_workspace_bytes(const kvq_cache* cache, int32_t n_q);
  * must hold at least n_q tokens.  With n_q = 1 the result equals
  * kvq_decode_attention's.  The queries of a kv head are read in groups of
  * up to 32 (query, head) rows, or of 256 where there are many, each group
- * one pass over the cache.
+ * one pass over the cache.  With many rows the number of splits, and with it
+ * the sums' order, also follows ws_bytes where the workspace holds fewer
+ * records than the fastest plan writes: calls that have to agree bit for bit
+ * take workspaces of one size.
  * Errors: KVQ_ERR_ARG (n_q out of range, a sequence shorter than n_q, null
  * pointers, misaligned workspace), KVQ_ERR_CAPACITY (workspace too small),
  * KVQ_ERR_HIP. */

@@ -2,8 +2,8 @@
 
 Every source is compiled by hipcc with packed fp32 ops disabled; the
 quantize-on-append source is also built with floating-point contraction
-off, so its fp64 quotients are plain IEEE divides and roundings.  The decode
-sources are built assuming no NaN operands (queries are finite, cached
+off: the exact remainder that decides a 4- or 8-bit code takes its roundings
+one by one, fused only where it says so.  The decode sources are built assuming no NaN operands (queries are finite, cached
 values are finite by construction, and the only infinity, the -inf start of
 a running maximum, never meets another): the maxima of the online softmax
 then need no quieting of their inputs.

@@ -212,7 +212,7 @@ decode_mfma_kernel(DecodeArgs a) {
   __shared__ uint32_t qt_s[NH][64];
   __shared__ float cs_s[NH];
   __shared__ __attribute__((aligned(16))) float p_lds[kWaves][kPRow * NH];  // weights to the value layout
-  __shared__ Reduce<GQ> red;
+  __shared__ __attribute__((aligned(16))) Reduce<GQ> red;
   // value operand halves of each byte of packed 2-bit codes (its 2-bit fields)
   constexpr int kTabWords = BV == 2 ? ValueTable2::kWords : 4;
   __shared__ __attribute__((aligned(16))) uint32_t vtab[kTabWords];

@@ -608,11 +608,14 @@ bool many_rows(const kvq_cache* c, int seq0, int nqry) {
 // smallest estimated time.  One workgroup of eight waves fills a compute
 // unit, so a launch takes rounds of one workgroup per unit; each costs its
 // blocks and a fixed part, and more than one split writes and re-reads the
-// records.  The constants fit K2V2 launches of 1024 to 16384 tokens at 512
-// queries of four heads per kv head and 1 to 4 splits within 5% (8192 tokens:
-// 309 us in one split, 173 in two, 129 in three, 111 in four).
-constexpr double kBlockUs = 1.16, kSplitUs = 13.0, kRecordUs = 3.0e-4;
+// records.  A block of 4- or 8-bit operands, which take two halves, has a time
+// of its own.  Against forced splits (1 to 16; K1V1, K2V2, K4V4 and K8V8, 128 and
+// 512 queries of four and eight heads, 512 to 16384 tokens) the plan is within
+// 5% of the fastest; K2V2, 512 queries of four heads over 8192 tokens: 353 us in
+// one split, 194 in two, 141 in three, 116 in four.
+constexpr double kBlockUs = 1.33, kBlockUs2 = 1.65, kSplitUs = 10.2, kRecordUs = 2.1e-4;
 int many_rows_blocks(const kvq_cache* c, const std::vector<int>& seqs, int nqry, int64_t max_records) {
+  const double block_us = c->bk[seqs[0]] + c->bv[seqs[0]] <= 4 ? kBlockUs : kBlockUs2;
   const int gqh = c->d.num_q_heads / c->d.num_kv_heads;
   const int nrg = (nqry + 32 / gqh - 1) / (32 / gqh), nrw = (nrg + kvq::kPrefillWaves - 1) / kvq::kPrefillWaves;
   const int64_t bound = splits_bound(c), units = (int64_t)c->d.num_kv_heads * nrw, cus = target_workgroups(1);
@@ -636,7 +639,7 @@ int many_rows_blocks(const kvq_cache* c, const std::vector<int>& seqs, int nqry,
     }
     if (records > max_records) break;
     const int64_t rounds = (wgs + cus - 1) / cus;
-    const double t = rounds * (bps * kBlockUs + kSplitUs) +
+    const double t = rounds * (bps * block_us + kSplitUs) +
                      records * (double)nqry * c->d.num_q_heads * kRecordUs;
     if (ns == 1 || t < best) best = t, pick = bps;
   }

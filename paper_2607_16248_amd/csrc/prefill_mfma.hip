@@ -25,7 +25,7 @@
 // A further product of P^T with [z; s; 1; z'] gives the zero-point terms and the
 // sum of the weights: s lifted like the operands, and the zero-points that are
 // subnormal lifted into rows z' of their own, since products of subnormal
-// halves lose bits (mfma_common.h).  Per 32 tokens and 16 rows: 8 + 8 + 2 MFMAs at one and
+// halves lose bits (mfma_common.h).  Per 32 tokens and 16 rows: 8 + 16 + 2 MFMAs at one and
 // two bits.  Key zero-point terms come from a table per wave, 16 key groups
 // at a time.
 //
@@ -33,15 +33,16 @@
 // keys and values are operands already.  A workgroup takes a range of blocks
 // (a split); a call with one split writes its output directly.
 //
-// What bounds it: a wave's block is 36 MFMAs (one and two bits; 576 cycles)
+// What bounds it: a wave's block is 52 MFMAs (one and two bits; 832 cycles)
 // and about 145 vector instructions, of which the exponentials and the hi and
 // lo packing are 80 and its share of the unpacking 45; two waves per SIMD
-// (235 registers) take 1.16 us for their blocks of 32 tokens, one alone 0.94,
-// so latencies still show.  A barrier every second block instead of every
-// block, with four operand buffers, gave 3%; the value operands read before
-// the packing 1%.  Measured, 512 queries of 32 heads on 8 kv heads, K2V2: over
-// 65536 tokens 668 us, 820 TFLOP/s (32-row groups 1980 us), over 8192 tokens
-// 111 us (312), over 512 tokens 29 us; K4V4 over 8192 tokens 145 us (302).
+// (242 registers) take 1.33 us for their blocks of 32 tokens (1.16 without the
+// values' products with the low halves), so latencies still show.  A barrier
+// every second block instead of every block, with four operand buffers, gave
+// 3%; the value operands read before the packing 1%.  Measured, 512 queries of
+// 32 heads on 8 kv heads, K2V2: over 65536 tokens 745 us, 735 TFLOP/s (32-row
+// groups 1980 us), over 8192 tokens 114 us (304), over 512 tokens 28 us; K4V4
+// over 8192 tokens 137 us (320).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -36,7 +36,7 @@ CASES = [
     (8, 4, 32, 128, 33, 2, (97, 31, 31, 64), False, 0),
     (1, 2, 32, 32, 32, 4, (90, 45, 45), True, 3),              # 2-byte aligned inputs
     (4, 8, 128, 32, 0, 1, (130, 126), True, 1),
-    (2, 2, 32, 8, 16, 4, (200, 60), True, 0),                  # canonical layouts
+    (2, 2, 32, 8, 16, 4, (200, 60), True, 0),                  # value groups of 8 and 16 channels
     (1, 1, 64, 16, 0, 4, (257,), True, 2),
     (4, 1, 128, 16, 90, 4, (400, 100), False, 0),
     (8, 2, 32, 128, 0, 4, (64, 3, 61), True, 0),

@@ -4,7 +4,7 @@ The cache arena, the decode and chunk workspaces, the outputs, the export
 and dequantization buffers each sit between two 64 KiB bands filled with a
 known byte; after every call (appends, fused append + decode, decode, its
 two phases, chunk queries, dequantization, export, release, reset) the bands
-must be unchanged.  Matrix-core and vector kernels, contiguous and paged
+must be unchanged.  Kernels of every class, contiguous and paged
 caches, fp16 windows.
 """
 import numpy as np

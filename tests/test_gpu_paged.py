@@ -9,8 +9,8 @@ the oracle and against the same inputs in a contiguous cache.
 - decode outputs bit-identical to the contiguous cache's (same split plan,
   same arithmetic) and within 2e-3 of the fp64 oracle;
 - chunk attention and kvq_dequant over paged caches;
-- the matrix kernels (1/2-bit, 4 and 8 bits) and the vector kernel
-  (canonical layout) both read through the table;
+- the kernels of decode_mfma.hip (1/2-bit, 4 and 8 bits) and the exact
+  kernel both read through the table;
 - a shared pool smaller than batch x capacity: an append that needs more
   pages fails up front, and succeeds after a release.
 """
@@ -206,7 +206,7 @@ def test_pool_larger_than_4_GiB():
     fills 464 pages (4.4 GB), so every page of sequence 1 starts beyond
     4 GiB of the pool.  The matrix kernel addresses each page through a
     resource of its own: outputs bit-identical to a contiguous cache (the
-    vector kernel would round differently), and sequence 1 within 2e-3 of
+    other kernel would round differently), and sequence 1 within 2e-3 of
     the oracle."""
     from paper_2607_16248_amd import kvq
     L0, L1, cap, P = 464 * 4096, 6000, 1 << 21, 4096

@@ -3,9 +3,8 @@ key and value groups whose scale is every positive finite fp16 value that
 fp16 inputs reach, approached exactly, from just above the value below, from
 just below and at the midpoint, with elements on exact rounding ties
 (min + (k + 1/2) s).  The packed bytes (codes, scales, zeros) must equal the
-oracle's canonical image, on the matrix-core layout (4 query heads per kv
-head) after one prefill and on the canonical layout (1 query head per kv
-head) after appends of 45 tokens at a time, which pack groups from the fp16
+oracle's canonical image, with 4 query heads per kv head after one
+prefill and with 1 query head per kv head after appends of 45 tokens at a time, which pack groups from the fp16
 ring."""
 import functools
 

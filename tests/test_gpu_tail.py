@@ -1,7 +1,7 @@
 """GPU parity of the fp16-tail split (decode and chunk queries) against the
 fp64 oracle: tails of one token to several blocks per wave, at the edges of
 its 32-token blocks, wrapped around the ring, with every head count on the
-matrix and the vector kernels, and fused appends that attend over the call's
+kernels of both classes, and fused appends that attend over the call's
 own tokens (inputs aligned to 4 bytes only) while storing them.  The bound is
 tight where every token is fp16: both products are exact but for fp32 sums
 and weights of 22 bits, 2^-20 relative with the sums of a few hundred terms."""
