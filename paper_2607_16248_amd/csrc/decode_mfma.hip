@@ -232,7 +232,7 @@ decode_mfma_kernel(DecodeArgs a) {
 
   if (wk.sp >= S.nq) {  // fp16 tail tokens
     TailState<1> st;
-    tail_split<1, GQ, CAUSAL>(a, S, wk.h, wk.rg, blk, st, lane, wv);
+    tail_split<1, GQ, CAUSAL, matrix_waves(BK, BV, BPG, GQ) == 4 ? 0 : 4>(a, S, wk.h, wk.rg, blk, st, lane, wv);
     stage_tail<GQ, 1>(st, 0, 0, red, lane, wv);
     __syncthreads();
     write_record<GQ, CAUSAL>(a, S, wk.h, wk.rg, wk.sp, red);

@@ -584,8 +584,8 @@ struct SplitPlan {
 
 // Whether a class's chunk queries go to the many-row kernel, by (query, head)
 // rows per kv head and, at 4-bit keys and values, by rows times tokens:
-//   1- and 2-bit classes from 80 rows on: 96 rows of 4096 tokens (K2V2) take 24
-//   against 37 us in 32-row groups, 64 rows of 32768 tokens 44 against 40;
+//   1- and 2-bit classes from 80 rows on: 80 rows of 4096 tokens (K2V2) take 24
+//   us, 76 in 32-row groups 34; of 32768 tokens 50 and 64, but 64 rows 40;
 //   K4V4 (which has 16-row groups of half the products per row) from 256 rows
 //   and 3 * 2^20 rows x tokens on: 512 rows of 8192 tokens 51 against 62 us, of
 //   4096 tokens 40 against 39, 256 rows of 1024 tokens 20 against 18;
