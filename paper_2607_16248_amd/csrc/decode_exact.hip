@@ -16,8 +16,9 @@
 // What bounds it: the vector unit, by the unpacking: 2 to 6 instructions per
 // operand dword, 64 or more dwords per 32-token block, against 40 to 60
 // products.  Each wave takes blocks of its own (key groups j0 + wave + 4n of
-// the split), the next block's loads in flight but for the 8-bit classes; two
-// waves per SIMD, no spills but K8V8's with groups of 8 or 16 (10 registers).
+// the split), the next block's loads in flight but for the widest classes
+// (kAhead); two waves per SIMD, spills of 10 registers in K8V8 with groups of 8
+// or 16 and of one or two in K1V8, K2V8 and K8V1 with wider ones.
 // The vector kernel it replaces multiplied each code by each row's query (64 *
 // rows multiply-adds per token half) from LDS.  Measured, 8 kv heads, split
 // kernel alone: 32768 tokens, four heads each, K4V2 16.9 us (vector 29.8),
